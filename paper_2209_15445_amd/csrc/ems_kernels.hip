@@ -65,9 +65,8 @@ __device__ inline uint32_t wave_reserve(uint32_t* counter, uint32_t count) {
 #ifndef EMS_CURSOR_CHUNK
 #define EMS_CURSOR_CHUNK 64
 #endif
-static_assert(EMS_CURSOR_CHUNK <= 1 || EMS_CURSOR_CHUNK >= 64, "a chunk must cover a whole wave's request");
-__device__ inline uint32_t take_next(uint32_t* cursor, bool want, uint32_t& lo, uint32_t& hi) {
-  if (EMS_CURSOR_CHUNK <= 1) return wave_reserve(cursor, want ? 1u : 0u);
+static_assert(EMS_CURSOR_CHUNK >= 64, "a chunk must cover a whole wave's request");
+__device__ inline uint32_t take_next(uint32_t* cursor, uint32_t pool, bool want, uint32_t& lo, uint32_t& hi) {
   const uint64_t m = __ballot(want);
   const uint32_t n = (uint32_t)__popcll(m);
   const uint32_t rank = (uint32_t)__popcll(m & __lanemask_lt());
@@ -78,7 +77,7 @@ __device__ inline uint32_t take_next(uint32_t* cursor, bool want, uint32_t& lo, 
     uint32_t base = 0;
     const int leader = __ffsll((unsigned long long)m) - 1;
     if ((int)__lane_id() == leader) base = atomicAdd(cursor, (uint32_t)EMS_CURSOR_CHUNK);
-    base = __shfl(base, leader);
+    base = __shfl(base, leader) + pool;
     if (rank >= avail) i = base + (rank - avail);
     lo = base + (n - avail);
     hi = base + EMS_CURSOR_CHUNK;
@@ -369,6 +368,30 @@ __device__ StepEnv<R> stage(const KArgs& a, char* lds_bytes, bool photons) {
 
 }  // namespace
 
+// How a launch's tracks are dealt to its waves: `lanes` lanes of a wave hold
+// tracks, the wave starts with the queue indices [first, first + lanes), and
+// indices from `pool` on are handed out by the launch's cursor.
+// A population that does not fill the device is dealt evenly over all waves:
+// what bounds such a launch is the chain of dependent steps of its slowest
+// wave, and a wave pays for every path that any of its lanes takes, so a wave
+// with one track runs its steps several times faster than one with 64.
+// 32 x 1 GeV (at most 6000 tracks at once, 2048 waves): 6.7 ms a batch with
+// 64 tracks to a wave, 3.2 ms dealt evenly.
+struct WaveShare {
+  uint32_t lanes, first, pool;
+};
+__device__ inline WaveShare wave_share(uint32_t n) {
+  const uint32_t waves = gridDim.x * (kBlock / 64);
+  // consecutive shares go to different blocks (and so to different CUs)
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+  WaveShare s;
+  const uint32_t even = n / waves + (n % waves != 0);
+  s.lanes = even >= 64u ? 64u : (even > 1u ? even : 1u);
+  s.first = w * s.lanes;
+  s.pool = waves * s.lanes;
+  return s;
+}
+
 // One iteration for the photons (PHOTONS) or for the e-/e+ (otherwise).
 //
 // Batched lane refill: the lanes of a wave keep stepping their tracks while
@@ -444,8 +467,8 @@ __global__ __launch_bounds__(kBlock, (visit_waves<PHOTONS, R, GEO, F>())) void k
   const uint32_t np_raw = (PHOTONS || !(F & kFShort)) ? 0u : ctl->n_spill;
   const uint32_t np = (uint64_t)np_raw < a.cap_p ? np_raw : (uint32_t)a.cap_p;
   const uint32_t nmine = PHOTONS ? n0 : n1 + n2 + np;
-  const uint32_t need = (nmine + kBlock - 1) / kBlock;
-  const bool work = blockIdx.x < need && ctl->error == 0;
+  const WaveShare share = wave_share(nmine);
+  const bool work = blockIdx.x * share.lanes < nmine && ctl->error == 0;
   constexpr int KIND = PHOTONS ? 0 : 1;
 
   if (work) {
@@ -472,7 +495,17 @@ __global__ __launch_bounds__(kBlock, (visit_waves<PHOTONS, R, GEO, F>())) void k
     bool fin = false;   // its visit ended; outputs wait for the batch commit
     bool held = false;  // the visit's last step is not yet applied to the tallies
     bool drained = false;
-    uint32_t chunk_lo = 0, chunk_hi = 0;  // queue indices held by this wave (uniform)
+    // queue indices held by this wave (uniform)
+    uint32_t chunk_lo = share.first, chunk_hi = share.first + share.lanes;
+    const bool my_lane = __lane_id() < share.lanes;
+    // Once the queue is used up nothing refills the lanes, and a wave that
+    // let all of its lanes finish before it sampled their interactions
+    // would hold the launch back by one chain of steps after another: it
+    // takes a batch as soon as at most 3/16 of its lanes still step (of 64:
+    // 12; 0, 4, 8, 16, 20, 24 measured on 1500 x 10 GeV with scattering and
+    // fluctuations: 27.7, 24.1, 23.5, 23.4, 23.4, 23.5 ms; 12: 23.3 ms).
+    const uint32_t drain_below = share.lanes * 3 / 16;
+    const uint32_t world_min = share.lanes / 4 < kWorldBatch ? share.lanes / 4 : kWorldBatch;
     int sp = PHOTONS ? 0 : 1;
     Trk<R> t, before;
     VisitState<R> vs;
@@ -500,7 +533,7 @@ __global__ __launch_bounds__(kBlock, (visit_waves<PHOTONS, R, GEO, F>())) void k
       uint32_t stepping = (uint32_t)__popcll(__ballot(has && !fin && !world_wait));
       if constexpr (GEO == 1) {
         const uint32_t nw = (uint32_t)__popcll(__ballot(world_wait));
-        if (nw && (nw >= kWorldBatch || stepping == 0)) {
+        if (nw && (nw >= world_min || stepping == 0)) {
           if (world_wait) {
             const double p[3] = {t.x, t.y, t.z}, u[3] = {(double)t.ux, (double)t.uy, (double)t.uz};
             world_pre.s = box_distance(env.nav, t.slab, p, u, world_pre.fc);
@@ -510,8 +543,8 @@ __global__ __launch_bounds__(kBlock, (visit_waves<PHOTONS, R, GEO, F>())) void k
           stepping += nw;
         }
       }
-      // batch point: few lanes still stepping (or none, once the queue is drained)
-      if (stepping <= (drained ? 0u : refill_below)) {
+      // batch point: few lanes still stepping
+      if (stepping == 0 || (drained ? stepping <= drain_below && __ballot(fin) != 0 : stepping <= refill_below)) {
         // (0) e-/e+: while the queue still has tracks, interactions are
         // sampled only once at least interact_min lanes wait for one (each
         // sampler costs the wave one pass however few lanes use it); until
@@ -526,15 +559,16 @@ __global__ __launch_bounds__(kBlock, (visit_waves<PHOTONS, R, GEO, F>())) void k
         // a parent that survives its interaction keeps its lane and goes on
         // stepping in this launch while it has steps left
         const bool will_continue = done && o.pending && parent_survives(o.process) && vs.steps < max_visit;
-        const bool want = (!has || (done && !will_continue)) && !drained;
+        const bool want = (!has || (done && !will_continue)) && !drained && my_lane;
         bool got = false;
         int nsp = PHOTONS ? 0 : 1;
         uint32_t nw = kDeadRecord;
         Trk<R> nt;
         if (__ballot(want) != 0) {
-          const uint32_t i = take_next(cursor, want, chunk_lo, chunk_hi);
+          const uint32_t i = take_next(cursor, share.pool, want, chunk_lo, chunk_hi);
           got = want && i < nmine;
-          drained = __ballot(want && i >= nmine) != 0;
+          // (with fewer than 64 lanes a wave the first shares hold every track)
+          drained = share.lanes < 64u || __ballot(want && i >= nmine) != 0;
           if (got) {
             uint32_t idx = i, home = PHOTONS ? h0 : h1;
             if (!PHOTONS && i >= n1) {

@@ -1,0 +1,26 @@
+"""A launch deals its tracks evenly over its waves: histories against the
+oracle at the edges of that rule (fewer tracks than waves, one to 64 tracks a
+wave with and without remainder, more than the waves hold at once), with few
+blocks so that small inputs reach them.  Bars: those of the random-track
+history test (energies 1e-11, deposits 5e-11 relative, positions 1e-9 mm)."""
+import pytest
+
+import ems_inputs as I
+from parity_util import compare_logs, ledger_residual
+from test_gpu_parity import E, run_gpu  # noqa: F401  (E: the module fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("blocks,n", [(1, 1), (1, 4), (1, 5), (1, 4 * 63 + 1), (1, 257), (1, 700), (3, 23), (0, 300)])
+def test_histories_at_the_edges_of_the_wave_shares(E, oracle_mod, blocks, n):  # noqa: F811
+    print(f"{n} tracks, {blocks} blocks", flush=True)
+    geo = I.calorimeter()
+    cfg = I.RunConfig(seed=23)
+    prim = I.random_tracks(n, n, geo, 1e-3, 50.0, seed=n)
+    ref = oracle_mod.Oracle(geo, cfg).run(prim, n_events=n, log_cap=4_000_000)
+    got = run_gpu(E, geo, cfg, prim, n, flags=E.F_STEPLOG | E.F_FULL_LEDGER, log_cap=1_000_000, blocks=blocks)
+    assert got["n_log"] <= 1_000_000
+    dev = compare_logs(got["log"], ref["log"], e_rtol=1e-11, pos_atol=1e-9, dep_rtol=5e-11)
+    print(f"steps {dev['n']}: {dev}", flush=True)
+    assert ledger_residual(got["edep"], got["ledger"], prim).max() < 1e-9
