@@ -648,6 +648,7 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
   a.n_mat = geo->n_materials;
   a.lds_g = lds_g;
   a.lds_l = lds_l;
+  a.lds_gl = lds_l + (uint32_t)gbytes;
   a.steps_per_visit = cfg->steps_per_visit;
   a.refill_below = cfg->refill_below;
   a.interact_min = cfg->interact_min;
@@ -665,18 +666,13 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
   const uint32_t need_l = (cfg->bz_tesla != 0.0 ? kFField : 0) |
                           (cfg->process_mask & EMS_P_MSC ? kFMsc : 0) | (cfg->process_mask & EMS_P_FLUCT ? kFFluct : 0) |
                           (compound ? kFCompound : 0) | (record ? kFRecord : 0);
-  const uint32_t need_g = (compound ? kFCompound : 0) | (record ? kFRecord : 0);
   constexpr uint32_t kAllParts = kFAll & ~kFShort;
-  a.feat_l = need_l == 0 ? 0u
-             : (geo->n_boxes == 0 && (need_l & ~(uint32_t)(kFField | kFRecord)) == 0) ? (uint32_t)(kFField | kFRecord)
-                                                                                      : kAllParts;
-  a.feat_g = need_g == 0 ? 0u : kAllParts;
+  a.feat = need_l == 0 ? 0u
+           : (geo->n_boxes == 0 && (need_l & ~(uint32_t)(kFField | kFRecord)) == 0) ? (uint32_t)(kFField | kFRecord)
+                                                                                    : kAllParts;
   // the short-electron routing is compiled into variants of its own
-  if (L.cap_s) {
-    a.feat_g |= kFShort;
-    a.feat_l |= kFShort;
-  }
-  if (cfg->flags & EMS_F_FULL_KERNELS) a.feat_g = a.feat_l = kFAll;
+  if (L.cap_s) a.feat |= kFShort;
+  if (cfg->flags & EMS_F_FULL_KERNELS) a.feat = kFAll;
   if (geo->n_boxes) {
     // device view of the hierarchy (same layout as the host one)
     a.env.nav = c->nav;
@@ -687,16 +683,27 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
     a.env.nav.nbr_off = reinterpret_cast<const uint32_t*>(c->ws + L.nbr_off);
     a.env.nav.nbr = reinterpret_cast<const uint32_t*>(c->ws + L.nbr);
   }
-  int per_g = 0, per_l = 0, per_s = 0;
-  if (visit_occupancy(a, &per_g, &per_l, &per_s) != hipSuccess || per_g < 1 || per_l < 1 || per_s < 1)
-    return bad(fail(EMS_E_DEVICE, "cannot configure the visit kernels"));
-  // one resident wave of blocks per launch; blocks grid-stride over the queue
+  // one visit launch an iteration for both species, unless their launches
+  // are timed one by one or the tables of both in LDS would cost resident
+  // blocks
+  int per_v = 0, per_both = 0, per_s = 0;
+  a.split = 1;
+  bool fits = visit_occupancy(a, 2u, &per_v) == hipSuccess && visit_occupancy(a, 0u, &per_s) == hipSuccess &&
+              per_v >= 1 && per_s >= 1;
+  if (fits && a.lds_gl <= 160u * 1024u && !(cfg->flags & EMS_F_KERNEL_TIMING)) {
+    a.split = 0;
+    if (visit_occupancy(a, 3u, &per_both) != hipSuccess || per_both < per_v) {
+      (void)hipGetLastError();
+      a.split = 1;
+      fits = visit_occupancy(a, 2u, &per_v) == hipSuccess;
+    }
+  }
+  if (!fits) return bad(fail(EMS_E_DEVICE, "cannot configure the visit kernels"));
+  // one resident wave of blocks per launch
   const uint32_t cus = (uint32_t)prop.multiProcessorCount;
-  c->blocks_g = cfg->launch_blocks ? cfg->launch_blocks : cus * (uint32_t)per_g;
-  c->blocks_l = cfg->launch_blocks ? cfg->launch_blocks : cus * (uint32_t)per_l;
+  c->blocks_v = cfg->launch_blocks ? cfg->launch_blocks : cus * (uint32_t)per_v;
   c->blocks_s = cfg->launch_blocks ? cfg->launch_blocks : cus * (uint32_t)per_s;
-  a.waves_g = c->blocks_g * 4;  // 256-thread blocks of 64-lane waves
-  a.waves_l = c->blocks_l * 4;
+  a.waves = c->blocks_v * 4;  // 256-thread blocks of 64-lane waves
   a.waves_s = c->blocks_s * 4;
 
   if (no_alloc) {
@@ -1191,9 +1198,9 @@ static hipError_t enqueue_chunk(ems_ctx* c, uint32_t K, bool timing) {
   for (uint32_t k = 0; k < K && e == hipSuccess; ++k) {
     if (c->args.cap_s) e = launch_short(c->args, c->blocks_s, c->stream);
     if (e == hipSuccess && timing) e = hipEventRecord(c->evk[3 * k + 1], c->stream);
-    if (e == hipSuccess) e = launch_visit(c->args, true, c->blocks_g, c->stream);
+    if (e == hipSuccess && c->args.split) e = launch_visit(c->args, 1u, c->blocks_v, c->stream);
     if (e == hipSuccess && timing) e = hipEventRecord(c->evk[3 * k + 2], c->stream);
-    if (e == hipSuccess) e = launch_visit(c->args, false, c->blocks_l, c->stream);
+    if (e == hipSuccess) e = launch_visit(c->args, c->args.split ? 2u : 3u, c->blocks_v, c->stream);
     if (e == hipSuccess && timing) e = hipEventRecord(c->evk[3 * k + 3], c->stream);
   }
   return e;

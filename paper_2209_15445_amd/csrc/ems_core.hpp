@@ -100,6 +100,12 @@ EMS_HD float xpow(float a, float b) { return powf(a, b); }
 EMS_HD double xpow(double a, double b) { return pow(a, b); }
 EMS_HD double xceil(double v) { return ceil(v); }
 
+// Fused multiply-adds written out where an expression holds more than one
+// product that could be fused: which one the compiler takes depends on the
+// code around it, and the same step has to round the same in every kernel.
+EMS_HD float xfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+EMS_HD double xfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // A uniform draw in the arithmetic type: the FP64 value itself, or that
 // value rounded to float and kept inside [2^-25, 1 - 2^-24] so that ln u is
 // finite and u < 1 (the same draws drive both forms).
@@ -181,12 +187,12 @@ EMS_HD V3T<R> about_axis(V3T<R> u, R cost, R sint, R phi) {
   R sp, cp;
   xsincos(phi, &sp, &cp);
   const R a = sint * cp, b = sint * sp;
-  const R t2 = u.x * u.x + u.y * u.y;
+  const R t2 = xfma(u.x, u.x, u.y * u.y);
   if (t2 > R(0)) {
     const R t = xsqrt(t2);
-    return V3T<R>{(u.x * u.z * a - u.y * b) / t + u.x * cost,
-                  (u.y * u.z * a + u.x * b) / t + u.y * cost,
-                  -t * a + u.z * cost};
+    return V3T<R>{xfma(u.x, cost, xfma(u.x * u.z, a, -(u.y * b)) / t),
+                  xfma(u.y, cost, xfma(u.y * u.z, a, u.x * b) / t),
+                  xfma(u.z, cost, -(t * a))};
   }
   if (u.z > R(0)) return V3T<R>{a, b, cost};
   return V3T<R>{-a, b, -cost};

@@ -56,35 +56,48 @@ EMS_HD Queue<R> queue_view(char* base, uint64_t cap, uint32_t buf, uint32_t sp) 
 // room for every survivor, so a step whose secondaries do not fit is simply
 // not taken: the track is carried unchanged and stepped again later (its
 // random numbers depend only on its id and step count).
+constexpr int kNextCounters = 8, kNextHome = 0, kNextSec = 3, kNextShort = 6, kNextSpill = 7;
+// launch tallies (Ctl::add), by species where [3]
+enum : int {
+  kAddSteps = 0,        // [3] steps taken
+  kAddVisits = 3,       // [3] track records loaded
+  kAddMade = 6,         // [3] secondaries written
+  kAddKept = 9,         // [3] records written to the home regions
+  kAddMadeBy = 12,      // [2] secondaries by launch (photon, e-/e+)
+  kAddCarried = 14,     // tracks carried unstepped
+  kAddMadeShort = 15,   // e- secondaries written to the short buffer (in kAddMade too)
+  kAddStepsShort = 16,  // steps of the short launch (in kAddSteps too)
+  kAdds = 17
+};
 struct Ctl {
   uint32_t cur;           // index of the current buffer (0/1)
   uint32_t n_home[3];     // current queues: tracks in the home region
   uint32_t n_sec[3];      // current queues: tracks in the secondary region
-  uint32_t next_home[3];  // append counters of the next queues
-  uint32_t next_sec[3];
+  // append counters: home (0..2) and secondary regions (3..5) of the next
+  // queues by species, next short buffer (6), and this iteration's spill
+  // buffer (7: tracks the short launch hands to the e-/e+ loop)
+  uint32_t next[kNextCounters];
   uint32_t blocks_done;   // completion ticket of the running launch
   uint32_t iteration;
   uint32_t live;          // tracks in the current queues (after the swap)
   uint32_t error;         // kErr* bits
   uint32_t peak[3];
-  uint32_t commits;       // steps taken in the running launch
-  uint32_t carried;       // live tracks carried unstepped in the running launch
-  uint32_t cursor[2];     // next queue index handed out (photon, e-/e+ launch)
+  uint32_t cursor[2];     // queue indices handed out (photons, e-/e+)
   unsigned long long steps[3], created[3], deferred, log_n;
   unsigned long long visits[3];  // track records loaded (one per visit)
   unsigned long long made_by[2];  // secondary records written (photon, e-/e+ launches)
   // Live records: the extents n_home + n_sec may include dead slots (unused
   // ends of wave-private append chunks); n_real counts the live tracks of
-  // the current queues, next_real those written to the next queues.
+  // the current queues.
   uint32_t n_real[3];
-  uint32_t next_real[3];
   unsigned long long exit_n;  // outgoing tracks recorded (may exceed the capacity)
   // Short electrons (KArgs::short_E): extent and live records of the
-  // current short buffer, append counters of the next one, the spill
-  // buffer's extent (tracks the short launch hands to this iteration's
-  // e-/e+ launch) and the short launch's cursor.
-  uint32_t n_short, n_short_real, next_short, next_short_real, n_spill, cursor_s;
+  // current short buffer.
+  uint32_t n_short, n_short_real;
   unsigned long long steps_s;  // e- steps taken by the short launches
+  // tallies of the running iteration, folded into the totals above when it
+  // ends
+  unsigned long long add[kAdds];
 };
 enum : uint32_t { kErrOverflow = 1u, kErrStall = 2u, kErrCorrupt = 4u };
 
@@ -143,17 +156,18 @@ struct KArgs {
   uint32_t profile_cap;
   uint32_t flags;
   uint32_t n_mat;
-  uint32_t lds_g, lds_l;      // dynamic LDS of the photon / lepton kernels
+  uint32_t lds_g, lds_l, lds_gl;  // dynamic LDS of a launch: photon, lepton tables, both
+  uint32_t split;             // photons and e-/e+ in a launch each
   uint32_t steps_per_visit;   // steps a thread may take per launch
   uint32_t refill_below;      // batch commit/refill when at most this many lanes still step
   uint32_t interact_min;      // e-/e+: sample a batch's interactions once this many wait
   uint32_t photon_steps_per_visit, photon_refill_below;  // the photon kernel's own two
   uint32_t precision;  // 0: FP64 kernels, 1: mixed kernels
-  uint32_t waves_g, waves_l;  // waves of the photon and of the e-/e+ launch
+  uint32_t waves;             // waves of a visit launch
   ExitRec* exits;             // outgoing tracks (exit_cap records)
   uint64_t exit_cap;
   uint32_t geo;               // geometry kind: 0 slab stack, 1 boxes
-  uint32_t feat_g, feat_l;    // optional parts (kF* bits) of the photon and e-/e+ kernels launched
+  uint32_t feat;              // optional parts (kF* bits) of the kernels launched
   uint32_t vol_bits;          // low bits of the packed word that hold the volume
   StepEnv<double> env;  // scalars; its pointers are set per block
   // Short electrons: e- secondaries below short_E (0: none) are appended to

@@ -4,10 +4,10 @@
 // kernel per species in three streams, appending secondaries to per-species
 // "next" index arrays with an atomic counter and swapping current/next after
 // each step (section 3).  On MI355X:
-//  - one launch per iteration for photons and one for e-/e+ (a concatenated
-//    index space [e- | e+]), in stream order, so the light photon kernel is
-//    not held to the lepton kernel's register budget and each stages only
-//    its own tables in LDS;
+//  - one launch per iteration: its waves are dealt to the photons and to the
+//    e-/e+ (a concatenated index space [e- | e+]), and go on with the other
+//    species when their own is used up, so neither species' last waves leave
+//    the device idle;
 //  - the queues hold the tracks themselves (SoA, coalesced); survivors are
 //    rewritten compactly each iteration, so slots are reused by construction;
 //  - a thread keeps stepping its track (a "visit") until a step creates
@@ -19,7 +19,7 @@
 //  - secondaries are reserved against a per-species limit that always leaves
 //    room for every survivor; a track whose secondaries do not fit is carried
 //    from before that step, so a full queue defers work instead of losing it;
-//  - the last block of the e-/e+ launch swaps the queues, so a chain of
+//  - the last block of the launch swaps the queues, so a chain of
 //    launches needs no host round trip.
 #include <hip/hip_runtime.h>
 
@@ -87,44 +87,73 @@ __device__ inline uint32_t take_next(uint32_t* cursor, uint32_t pool, bool want,
   return i;
 }
 
-// Append slots in wave-private chunks.  A wave holds a range [lo, hi) of an
-// append counter and refills it `chunk` slots at a time (one global atomic
-// per chunk instead of one per batch: thousands of waves appending to the
-// same few counters otherwise serialise on them).  take_slots reserves cnt
-// (0..3) slots per lane and returns the lane's first position x in the
-// wave's request; its k-th slot is slot_of(tk, x + k).  Unused ends of the
-// ranges are marked dead when the wave exits.  chunk = 1 is exact
-// reservation (no unused slots).
-struct Take {
-  uint32_t lo, avail, base;
+// Append slots in wave-private chunks.  A wave holds a range [lo, hi) of each
+// append counter (Ctl::next) and refills it `chunk` slots at a time (one
+// global atomic per chunk instead of one per batch: thousands of waves
+// appending to the same few counters otherwise serialise on them).  Unused
+// ends of the ranges are marked dead when the wave exits.  chunk = 1 is
+// exact reservation (no unused slots).
+struct Ranges {
+  uint32_t lo[kNextCounters], hi[kNextCounters];  // uniform
 };
-__device__ inline uint32_t take_slots(uint32_t* counter, uint32_t cnt, uint32_t chunk, uint32_t& lo, uint32_t& hi,
-                                      Take& tk) {
+// A wave's request to one counter: cnt (0..3) slots per lane; the lane's
+// k-th slot is slot(k).
+struct Take {
+  uint32_t prefix, total, lo, avail, base;
+  __device__ uint32_t slot(uint32_t k) const {
+    const uint32_t x = prefix + k;
+    return x < avail ? lo + x : base + (x - avail);
+  }
+};
+__device__ inline Take ask(const Ranges& rg, int c, uint32_t cnt) {
   const uint64_t b0 = __ballot(cnt & 1u);
   const uint64_t b1 = __ballot((cnt >> 1) & 1u);
-  const uint32_t total = (uint32_t)(__popcll(b0) + 2 * __popcll(b1));
   const uint64_t lt = __lanemask_lt();
-  const uint32_t prefix = (uint32_t)(__popcll(b0 & lt) + 2 * __popcll(b1 & lt));
-  tk.lo = lo;
-  tk.avail = hi - lo;
-  tk.base = 0;
-  if (total > tk.avail) {
-    const uint32_t need = total - tk.avail;
-    const uint32_t grab = need > chunk ? need : chunk;
-    const int leader = __ffsll((unsigned long long)(b0 | b1)) - 1;
-    uint32_t base = 0;
-    if ((int)__lane_id() == leader) base = atomicAdd(counter, grab);
-    base = __builtin_amdgcn_readfirstlane(__shfl(base, leader));
-    tk.base = base;
-    lo = base + need;
-    hi = base + grab;
-  } else {
-    lo += total;
-  }
-  return prefix;
+  Take t;
+  t.total = (uint32_t)(__popcll(b0) + 2 * __popcll(b1));
+  t.prefix = (uint32_t)(__popcll(b0 & lt) + 2 * __popcll(b1 & lt));
+  t.lo = rg.lo[c];
+  t.avail = rg.hi[c] - rg.lo[c];
+  t.base = 0;
+  return t;
 }
-__device__ inline uint32_t slot_of(const Take& tk, uint32_t x) {
-  return x < tk.avail ? tk.lo + x : tk.base + (x - tk.avail);
+// Serve up to five requests at once: the counters that have to be refilled
+// are incremented by one instruction, lane c for counter c.  The increments
+// complete at the memory side, some microseconds away: one after another
+// they were most of a batch in a wave with few tracks.
+struct Ask {
+  int c;
+  uint32_t chunk;
+  Take* t;
+};
+template <int N>
+__device__ inline void serve(Ctl* ctl, Ranges& rg, const Ask (&a)[N]) {
+  uint32_t need[N], grab[N], any = 0, v = 0;
+  const uint32_t lane = __lane_id();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const Take& t = *a[i].t;
+    need[i] = t.total > t.avail ? t.total - t.avail : 0u;
+    grab[i] = need[i] == 0u ? 0u : (need[i] > a[i].chunk ? need[i] : a[i].chunk);
+    any |= need[i];
+    if (lane == (uint32_t)a[i].c) v = grab[i];
+  }
+  uint32_t got = 0;
+  if (any) {
+    if (v) got = atomicAdd(&ctl->next[lane], v);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int c = a[i].c;
+    if (need[i]) {
+      const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)got, c);
+      a[i].t->base = base;
+      rg.lo[c] = base + need[i];
+      rg.hi[c] = base + grab[i];
+    } else {
+      rg.lo[c] += a[i].t->total;
+    }
+  }
 }
 
 // Per-iteration append plan of species q (the same in both launches of an
@@ -159,19 +188,18 @@ __device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uin
     for (int q = 0; q < 3; ++q) {
       const uint64_t n = q == 0 ? n0 : (q == 1 ? n1 : n2);
       const uint64_t room = a.cap - n;
-      const uint64_t waves = (uint64_t)a.waves_g + a.waves_l;
+      const uint64_t waves = 2ull * a.waves;
       const uint64_t budget = (n < room ? n : room) / 4;
       uint32_t chunk = EMS_APPEND_CHUNK;
       while (chunk > 1 && waves * chunk > budget) chunk >>= 1;
-      const uint64_t home_waves = q == 0 ? a.waves_g : a.waves_l;
       p.chunk[q] = chunk;
-      p.lim[q] = (uint32_t)(room - (chunk > 1 ? home_waves * chunk : 0));  // slack <= room / 4
+      p.lim[q] = (uint32_t)(room - (chunk > 1 ? (uint64_t)a.waves * chunk : 0));  // slack <= room / 4
     }
     p.lim_s = 0;
     p.chunk_s = 1;
     return p;
   }
-  const uint64_t waves = (uint64_t)a.waves_g + a.waves_l + (a.cap_s ? a.waves_s : 0u);
+  const uint64_t waves = 2ull * a.waves + (a.cap_s ? a.waves_s : 0u);
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     const uint64_t n = q == 0 ? n0 : (q == 1 ? (uint64_t)n1 + ns : n2);
@@ -179,7 +207,7 @@ __device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uin
     const uint64_t budget = (n < room ? n : room) / 4;
     uint32_t chunk = EMS_APPEND_CHUNK;
     while (chunk > 1 && waves * chunk > budget) chunk >>= 1;
-    const uint64_t home_waves = q == 0 ? a.waves_g : (q == 1 && a.cap_s ? a.waves_l + a.waves_s : a.waves_l);
+    const uint64_t home_waves = (uint64_t)a.waves + (q == 1 && a.cap_s ? a.waves_s : 0u);
     const uint64_t slack = chunk > 1 ? home_waves * chunk : 0;
     p.chunk[q] = chunk;
     p.lim[q] = (uint32_t)(room > slack ? room - slack : 0);
@@ -217,15 +245,30 @@ __device__ inline uint32_t wave_sum(uint32_t v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
-
-// sum over the wave of a per-lane count, one atomic by lane 0
-__device__ inline void wave_count(unsigned long long* counter, uint32_t v) {
-  const uint32_t s = wave_sum(v);
-  if (__lane_id() == 0 && s) atomicAdd(counter, (unsigned long long)s);
-}
 __device__ inline void wave_count(uint32_t* counter, uint32_t v) {
   const uint32_t s = wave_sum(v);
   if (__lane_id() == 0 && s) atomicAdd(counter, s);
+}
+
+// Launch tallies (Ctl::add): lanes add to the block's copy in LDS, and the
+// block adds its copy to the launch's with one instruction when it ends.
+__device__ inline void clear_counts(unsigned long long* cnt) {
+  if (threadIdx.x < kAdds) cnt[threadIdx.x] = 0ull;
+}
+__device__ inline void count(unsigned long long* cnt, int k, uint32_t v) {
+  if (v) atomicAdd(&cnt[k], (unsigned long long)v);
+}
+// all waves of the block have counted (a barrier inside)
+__device__ inline void publish_counts(Ctl* ctl, const unsigned long long* cnt) {
+  __syncthreads();
+  if (threadIdx.x < kAdds) {
+    const unsigned long long v = cnt[threadIdx.x];
+    // (the old value is waited for, so the addition is done)
+    if (v) {
+      const unsigned long long old = atomicAdd(&ctl->add[threadIdx.x], v);
+      asm volatile("" ::"v"((uint32_t)old));
+    }
+  }
 }
 
 template <class R>
@@ -337,16 +380,24 @@ struct DevSink {
   }
 };
 
-// Stage a table block, the slab planes, slab materials and material
-// constants in LDS; returns the environment pointing there.
+// Stage the table blocks of the launch's species (bit 0 of `which`: photons,
+// bit 1: e-/e+), the slab planes, slab materials and material constants in
+// LDS; returns the environment pointing there.
+enum : uint32_t { kPhotons = 1u, kLeptons = 2u };
+template <class R>
+__device__ inline R* stage_tables(const void* src, uint32_t n, char*& lds) {
+  R* dst = reinterpret_cast<R*>(lds);
+  const R* t = static_cast<const R*>(src);
+  for (uint32_t i = threadIdx.x; i < n; i += kBlock) dst[i] = t[i];
+  lds += (n * sizeof(R) + 7) / 8 * 8;
+  return dst;
+}
 template <class R, int GEO>
-__device__ StepEnv<R> stage(const KArgs& a, char* lds_bytes, bool photons) {
-  const uint32_t nt = photons ? kGammaTables : kLeptonTables;
-  const uint32_t ntab = a.n_mat * nt * a.env.nodes;
-  const R* src = static_cast<const R*>(photons ? a.tab_g : a.tab_l);
-  R* lds = reinterpret_cast<R*>(lds_bytes);
-  for (uint32_t i = threadIdx.x; i < ntab; i += kBlock) lds[i] = src[i];
-  double* zp = reinterpret_cast<double*>(lds_bytes + (ntab * sizeof(R) + 7) / 8 * 8);
+__device__ StepEnv<R> stage(const KArgs& a, char* lds, uint32_t which) {
+  StepEnv<R> env = retype<R>(a.env);
+  if (which & kPhotons) env.tg = stage_tables<R>(a.tab_g, a.n_mat * kGammaTables * a.env.nodes, lds);
+  if (which & kLeptons) env.tl = stage_tables<R>(a.tab_l, a.n_mat * kLeptonTables * a.env.nodes, lds);
+  double* zp = reinterpret_cast<double*>(lds);
   // a box geometry reads its volume materials from global memory
   const uint32_t nz = GEO == 1 ? 0u : a.env.n_slabs + 1, nsm = GEO == 1 ? 0u : a.env.n_slabs;
   for (uint32_t i = threadIdx.x; i < nz; i += kBlock) zp[i] = a.zplane[i];
@@ -355,9 +406,6 @@ __device__ StepEnv<R> stage(const KArgs& a, char* lds_bytes, bool photons) {
   uint32_t* sm = reinterpret_cast<uint32_t*>(mr + a.n_mat);
   for (uint32_t i = threadIdx.x; i < nsm; i += kBlock) sm[i] = a.slab_mat[i];
   __syncthreads();
-  StepEnv<R> env = retype<R>(a.env);
-  env.tg = photons ? lds : nullptr;
-  env.tl = photons ? nullptr : lds;
   env.zplane = GEO == 1 ? nullptr : zp;
   env.mat = mr;
   env.elc = a.el_c;
@@ -368,10 +416,11 @@ __device__ StepEnv<R> stage(const KArgs& a, char* lds_bytes, bool photons) {
 
 }  // namespace
 
-// How a launch's tracks are dealt to its waves: `lanes` lanes of a wave hold
-// tracks, the wave starts with the queue indices [first, first + lanes), and
-// indices from `pool` on are handed out by the launch's cursor.
-// A population that does not fill the device is dealt evenly over all waves:
+// How one species' tracks are dealt to `waves` of a launch's waves: `lanes`
+// lanes of a wave hold tracks, wave w of them starts with the queue indices
+// [first, first + lanes), and indices from `pool` on are handed out by the
+// launch's cursor.
+// A population that does not fill the device is dealt evenly over the waves:
 // what bounds such a launch is the chain of dependent steps of its slowest
 // wave, and a wave pays for every path that any of its lanes takes, so a wave
 // with one track runs its steps several times faster than one with 64.
@@ -380,10 +429,7 @@ __device__ StepEnv<R> stage(const KArgs& a, char* lds_bytes, bool photons) {
 struct WaveShare {
   uint32_t lanes, first, pool;
 };
-__device__ inline WaveShare wave_share(uint32_t n) {
-  const uint32_t waves = gridDim.x * (kBlock / 64);
-  // consecutive shares go to different blocks (and so to different CUs)
-  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+__device__ inline WaveShare wave_share(uint32_t n, uint32_t w, uint32_t waves) {
   WaveShare s;
   const uint32_t even = n / waves + (n % waves != 0);
   s.lanes = even >= 64u ? 64u : (even > 1u ? even : 1u);
@@ -391,8 +437,7 @@ __device__ inline WaveShare wave_share(uint32_t n) {
   s.pool = waves * s.lanes;
   return s;
 }
-
-// One iteration for the photons (PHOTONS) or for the e-/e+ (otherwise).
+// The visits of one species in one iteration: photons (PHOTONS) or e-/e+.
 //
 // Batched lane refill: the lanes of a wave keep stepping their tracks while
 // more than refill_below (photons: photon_refill_below) of them are still
@@ -404,509 +449,585 @@ __device__ inline WaveShare wave_share(uint32_t n) {
 // which tracks are visited does not change any result.
 
 // Minimum resident waves per SIMD the register allocation must allow, per
-// kernel, arithmetic type and geometry kind.
-#ifndef EMS_WAVES_F64_PHOTON
-#define EMS_WAVES_F64_PHOTON 2
+// arithmetic type, geometry kind and optional parts.  FP64: 2 (at 3 the
+// kernels spill 1 KB per lane: e-/e+ 31% slower).  FP32, slab stack: 3
+// without optional parts (40 000 x 10 GeV 135 ms, at 2 157 ms); with them
+// (every such variant has the field part) and in box geometries 2 (1501
+// mixed-species events in a field 21.8 ms, at 3, with spills, 24.2 ms;
+// towers 999 x 1 GeV 13.0 ms, at 3 14.5 ms).
+#ifndef EMS_WAVES_F64
+#define EMS_WAVES_F64 2
 #endif
-#ifndef EMS_WAVES_F64_LEPTON
-#define EMS_WAVES_F64_LEPTON 2
+#ifndef EMS_WAVES_F32
+#define EMS_WAVES_F32 3
 #endif
-#ifndef EMS_WAVES_F32_PHOTON
-#define EMS_WAVES_F32_PHOTON 3  // fits in 168 registers; at 169 it would drop to 2 waves, 22% slower
+#ifndef EMS_WAVES_F32_FIELD
+#define EMS_WAVES_F32_FIELD 2
 #endif
-#ifndef EMS_WAVES_F32_LEPTON
-#define EMS_WAVES_F32_LEPTON 3  // 168 registers, a few spills: 8% faster than 2 waves of 205
+#ifndef EMS_WAVES_BOX_F32
+#define EMS_WAVES_BOX_F32 2
 #endif
-// Box geometries: photon steps wait on dependent loads of box records; with
-// the world volume's boundary distances computed for many lanes at once,
-// the photon kernels gain more from running without register spills (FP64
-// at 2 waves: 168 VGPRs and 132 spilled at 3; towers photon launch 2.85 ms
-// instead of 3.44 ms; FP32 at 3: 2.58 ms instead of 2.90 ms at 4).  More
-// waves made the e-/e+ kernels slower; the FP32 one runs at 2 rather than 3
-// (towers e-/e+ launch 1.98 ms instead of 2.11 ms; photons at 2: slower).
-#ifndef EMS_WAVES_BOX_F64_PHOTON
-#define EMS_WAVES_BOX_F64_PHOTON 2
-#endif
-#ifndef EMS_WAVES_BOX_F64_LEPTON
-#define EMS_WAVES_BOX_F64_LEPTON EMS_WAVES_F64_LEPTON
-#endif
-#ifndef EMS_WAVES_BOX_F32_PHOTON
-#define EMS_WAVES_BOX_F32_PHOTON 3
-#endif
-#ifndef EMS_WAVES_BOX_F32_LEPTON
-#define EMS_WAVES_BOX_F32_LEPTON 2
-#endif
-// The FP32 e-/e+ slab kernels with optional parts (every such variant has
-// the field part) need more registers: at 3 waves they spill 100-176 bytes
-// per lane, at 2 they spill none.  With 2: the mixed species in a field
-// +4.3%, PbWO4 +3.5%, scattering and fluctuations +4.2%, the offload server
-// +6.6% (mixed form); the beam's kernel (no optional parts) keeps 3.
-#ifndef EMS_WAVES_F32_LEPTON_FIELD
-#define EMS_WAVES_F32_LEPTON_FIELD 2
-#endif
-template <bool PHOTONS, class R, int GEO, int F = 0>
+template <class R, int GEO, int F>
 constexpr int visit_waves() {
-  if (!PHOTONS && GEO == 0 && sizeof(R) == 4 && (F & kFField) != 0) return EMS_WAVES_F32_LEPTON_FIELD;
-  if (GEO == 1)
-    return sizeof(R) == 8 ? (PHOTONS ? EMS_WAVES_BOX_F64_PHOTON : EMS_WAVES_BOX_F64_LEPTON)
-                          : (PHOTONS ? EMS_WAVES_BOX_F32_PHOTON : EMS_WAVES_BOX_F32_LEPTON);
-  return sizeof(R) == 8 ? (PHOTONS ? EMS_WAVES_F64_PHOTON : EMS_WAVES_F64_LEPTON)
-                        : (PHOTONS ? EMS_WAVES_F32_PHOTON : EMS_WAVES_F32_LEPTON);
+  if (sizeof(R) == 8) return EMS_WAVES_F64;
+  if (GEO == 1) return EMS_WAVES_BOX_F32;
+  return (F & kFField) != 0 ? EMS_WAVES_F32_FIELD : EMS_WAVES_F32;
 }
+// What the waves of a launch share: the current queues' sizes, the append
+// plan, and where the launch's tallies go.
+struct Launch {
+  uint32_t cur, h0, h1, h2, n0, n1, n2, np;
+  Plan plan;
+  unsigned long long* cnt;  // block's tallies (LDS)
+};
+
 template <bool PHOTONS, class R, int GEO, int F>
-__global__ __launch_bounds__(kBlock, (visit_waves<PHOTONS, R, GEO, F>())) void k_visit(KArgs a) {
-  extern __shared__ double lds_words[];
-  char* lds = reinterpret_cast<char*>(lds_words);
-  Ctl* ctl = a.ctl;
-  const uint32_t cur = ctl->cur;
-  const uint32_t h0 = ctl->n_home[0], h1 = ctl->n_home[1], h2 = ctl->n_home[2];
-  const uint32_t n0 = h0 + ctl->n_sec[0], n1 = h1 + ctl->n_sec[1], n2 = h2 + ctl->n_sec[2];
-  constexpr bool kShort = (F & kFShort) != 0;
-  const uint32_t ns = kShort ? ctl->n_short : 0u;
-  // the e-/e+ launch also takes the tracks the short launch spilled
-  const uint32_t np_raw = (PHOTONS || !(F & kFShort)) ? 0u : ctl->n_spill;
-  const uint32_t np = (uint64_t)np_raw < a.cap_p ? np_raw : (uint32_t)a.cap_p;
-  const uint32_t nmine = PHOTONS ? n0 : n1 + n2 + np;
-  const WaveShare share = wave_share(nmine);
-  const bool work = blockIdx.x * share.lanes < nmine && ctl->error == 0;
+__device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepEnv<R>& env, const Launch& ln,
+                                           const WaveShare& share, Ranges& rg) {
   constexpr int KIND = PHOTONS ? 0 : 1;
+  constexpr bool kShort = (F & kFShort) != 0;
+  // a step changes the direction itself (before any interaction)
+  constexpr bool kTurns = !PHOTONS && (F & (kFField | kFMsc)) != 0;
+  // secondaries: photons make e- and e+, e-/e+ make photons and e-
+  constexpr int kSecA = PHOTONS ? kElectron : kGamma, kSecB = PHOTONS ? kPositron : kElectron;
+  const uint32_t nmine = PHOTONS ? ln.n0 : ln.n1 + ln.n2 + ln.np;
+  const uint32_t nxt = ln.cur ^ 1u;
+  const int max_visit = (int)(PHOTONS ? a.photon_steps_per_visit : a.steps_per_visit);
+  const uint32_t refill_below = PHOTONS ? a.photon_refill_below : a.refill_below;
+  const Plan& plan = ln.plan;
+  // short-electron routing: compiled into the kFShort variants only
+  const bool shorts = kShort && a.cap_s != 0;
+  DevSink sink{a.edep, a.ledger, ctl, a.log, a.log_cap, a.env.n_slabs,
+               (a.flags & kFlagFullLedger) != 0, (a.flags & kFlagSteplog) != 0, 0, 0.0,
+               a.exits, a.exit_cap};
+  uint32_t* cursor = &ctl->cursor[PHOTONS ? 0 : 1];
+  const bool track_live = (F & kFRecord) && (a.flags & kFlagEventLive) != 0;
 
-  if (work) {
-    const StepEnv<R> env = stage<R, GEO>(a, lds, PHOTONS);
-    const uint32_t nxt = cur ^ 1u;
-    const int max_visit = (int)(PHOTONS ? a.photon_steps_per_visit : a.steps_per_visit);
-    const uint32_t refill_below = PHOTONS ? a.photon_refill_below : a.refill_below;
-    // secondary slots per species that leave room for all survivors
-    const Plan plan = append_plan<kShort>(a, n0, n1, n2, ns);
-    const uint32_t lim0 = plan.lim[0], lim1 = plan.lim[1], lim2 = plan.lim[2];
-    // wave-private append ranges (uniform): secondaries and home, per
-    // species, and the next short buffer
-    uint32_t slo[3] = {0, 0, 0}, shi[3] = {0, 0, 0}, hlo[3] = {0, 0, 0}, hhi[3] = {0, 0, 0};
-    uint32_t sslo = 0, sshi = 0;
-    // short-electron routing: compiled into the kFShort variants only
-    const bool shorts = kShort && a.cap_s != 0;
-    DevSink sink{a.edep, a.ledger, ctl, a.log, a.log_cap, a.env.n_slabs,
-                 (a.flags & kFlagFullLedger) != 0, (a.flags & kFlagSteplog) != 0, 0, 0.0,
-                 a.exits, a.exit_cap};
-    uint32_t* cursor = &ctl->cursor[PHOTONS ? 0 : 1];
-    const bool track_live = (F & kFRecord) && (a.flags & kFlagEventLive) != 0;
-
-    bool has = false;   // lane holds a track (inside a visit or waiting to commit)
-    bool fin = false;   // its visit ended; outputs wait for the batch commit
-    bool held = false;  // the visit's last step is not yet applied to the tallies
-    bool drained = false;
-    // queue indices held by this wave (uniform)
-    uint32_t chunk_lo = share.first, chunk_hi = share.first + share.lanes;
-    const bool my_lane = __lane_id() < share.lanes;
-    // Once the queue is used up nothing refills the lanes, and a wave that
-    // let all of its lanes finish before it sampled their interactions
-    // would hold the launch back by one chain of steps after another: it
-    // takes a batch as soon as at most 3/16 of its lanes still step (of 64:
-    // 12; 0, 4, 8, 16, 20, 24 measured on 1500 x 10 GeV with scattering and
-    // fluctuations: 27.7, 24.1, 23.5, 23.4, 23.4, 23.5 ms; 12: 23.3 ms).
-    const uint32_t drain_below = share.lanes * 3 / 16;
-    const uint32_t world_min = share.lanes / 4 < kWorldBatch ? share.lanes / 4 : kWorldBatch;
-    int sp = PHOTONS ? 0 : 1;
-    Trk<R> t, before;
-    VisitState<R> vs;
-    StepOut<R> o;
-    o.nsec = 0;
-    uint32_t visits_e = 0, visits_p = 0, steps_e = 0, steps_p = 0, carried_n = 0;
-    uint32_t made0 = 0, made1 = 0, made2 = 0, made_s = 0;
-    uint32_t kept_a = 0, kept_b = 0;  // home records written (own species; e+)
-    // Box geometries: a step that starts in the world volume needs the
-    // nearest box along the track, a walk of the hierarchy that costs the
-    // whole wave as much as many ordinary steps however few lanes take it.
-    // Such lanes wait (world_wait), also across batches, until kWorldBatch
-    // of them do or no other lane steps; then the wave computes their
-    // distances together (world_ready, world_pre) and they take their steps
-    // with them.
-    bool world_ready = false;
-    GeoPre world_pre{0.0, Face{0, 0.0, 0, -1}};
-    // (charged tracks in a field search their boundary along the helix
-    // within their own step limit: they take no straight-line distance)
-    const bool world_batch = PHOTONS || !((F & kFField) && env.bz != 0.0);
-    for (;;) {
-      bool world_wait = false;
-      if constexpr (GEO == 1)
-        world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == env.nav.n_boxes;
-      uint32_t stepping = (uint32_t)__popcll(__ballot(has && !fin && !world_wait));
-      if constexpr (GEO == 1) {
-        const uint32_t nw = (uint32_t)__popcll(__ballot(world_wait));
-        if (nw && (nw >= world_min || stepping == 0)) {
-          if (world_wait) {
-            const double p[3] = {t.x, t.y, t.z}, u[3] = {(double)t.ux, (double)t.uy, (double)t.uz};
-            world_pre.s = box_distance(env.nav, t.slab, p, u, world_pre.fc);
-            world_ready = true;
-            world_wait = false;
+  bool has = false;   // lane holds a track (inside a visit or waiting to commit)
+  bool fin = false;   // its visit ended; outputs wait for the batch commit
+  bool held = false;  // the visit's last step is not yet applied to the tallies
+  bool drained = false;
+  // queue indices held by this wave (uniform)
+  uint32_t chunk_lo = share.first, chunk_hi = share.first + share.lanes;
+  if (share.first >= share.pool) chunk_hi = chunk_lo;  // a helper has no share of its own
+  const bool my_lane = __lane_id() < share.lanes;
+  // Once the queue is used up nothing refills the lanes, and a wave that
+  // let all of its lanes finish before it sampled their interactions
+  // would hold the launch back by one chain of steps after another: it
+  // takes a batch as soon as at most 3/16 of its lanes still step (of 64:
+  // 12; 0, 4, 8, 16, 20, 24 measured on 1500 x 10 GeV with scattering and
+  // fluctuations: 27.7, 24.1, 23.5, 23.4, 23.4, 23.5 ms; 12: 23.3 ms).
+  const uint32_t drain_below = share.lanes * 3 / 16;
+  const uint32_t world_min = share.lanes / 4 < kWorldBatch ? share.lanes / 4 : kWorldBatch;
+  int sp = PHOTONS ? 0 : 1;
+  Trk<R> t;
+  // the track before its last step, for a step whose secondaries do not
+  // fit (id, event and key do not change; the volume is o.slab, the step
+  // number t.n - 1)
+  double x0 = 0.0, y0 = 0.0, z0 = 0.0, e0 = 0.0;
+  R ux0 = R(0), uy0 = R(0), uz0 = R(0);
+  VisitState<R> vs;
+  StepOut<R> o;
+  o.nsec = 0;
+  o.pending = false;
+  uint32_t visits_e = 0, visits_p = 0, steps_e = 0, steps_p = 0, carried_n = 0;
+  uint32_t made_a = 0, made_b = 0, made_s = 0;
+  uint32_t kept_a = 0, kept_b = 0;  // home records written (own species; e+)
+  // Box geometries: a step that starts in the world volume needs the
+  // nearest box along the track, a walk of the hierarchy that costs the
+  // whole wave as much as many ordinary steps however few lanes take it.
+  // Such lanes wait (world_wait), also across batches, until kWorldBatch
+  // of them do (a quarter of a wave with fewer lanes) or no other lane
+  // steps; then the wave computes their distances together (world_ready,
+  // world_pre) and they take their steps with them.
+  bool world_ready = false;
+  GeoPre world_pre{0.0, Face{0, 0.0, 0, -1}};
+  // (charged tracks in a field search their boundary along the helix
+  // within their own step limit: they take no straight-line distance)
+  const bool world_batch = PHOTONS || !((F & kFField) && env.bz != 0.0);
+  for (;;) {
+    bool world_wait = false;
+    if constexpr (GEO == 1)
+      world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == env.nav.n_boxes;
+    uint32_t stepping = (uint32_t)__popcll(__ballot(has && !fin && !world_wait));
+    if constexpr (GEO == 1) {
+      const uint32_t nw = (uint32_t)__popcll(__ballot(world_wait));
+      if (nw && (nw >= world_min || stepping == 0)) {
+        if (world_wait) {
+          const double p[3] = {t.x, t.y, t.z}, u[3] = {(double)t.ux, (double)t.uy, (double)t.uz};
+          world_pre.s = box_distance(env.nav, t.slab, p, u, world_pre.fc);
+          world_ready = true;
+          world_wait = false;
+        }
+        stepping += nw;
+      }
+    }
+    // batch point: few lanes still stepping
+    if (stepping == 0 || (drained ? stepping <= drain_below && __ballot(fin) != 0 : stepping <= refill_below)) {
+      // (0) e-/e+: while the queue still has tracks, interactions are
+      // sampled only once at least interact_min lanes wait for one (each
+      // sampler costs the wave one pass however few lanes use it); until
+      // then those lanes are parked: they keep their tracks and take no
+      // part in this batch.  A wave whose lanes are all parked samples
+      // them, so every wave ends (interact_min <= 64).
+      const uint32_t npend = PHOTONS ? 0u : (uint32_t)__popcll(__ballot(fin && o.pending));
+      const bool parked = !PHOTONS && !drained && npend < a.interact_min && fin && o.pending;
+      const bool done = fin && !parked;  // visits this batch finishes
+      // (1) prefetch the records of the tracks that the lanes free after
+      // this batch will take; the loads are in flight during (2)
+      // a parent that survives its interaction keeps its lane and goes on
+      // stepping in this launch while it has steps left
+      const bool will_continue = done && o.pending && parent_survives(o.process) && vs.steps < max_visit;
+      const bool want = (!has || (done && !will_continue)) && !drained && my_lane;
+      bool got = false;
+      int nsp = PHOTONS ? 0 : 1;
+      uint32_t nw = kDeadRecord;
+      Trk<R> nt;
+      if (__ballot(want) != 0) {
+        const uint32_t i = take_next(cursor, share.pool, want, chunk_lo, chunk_hi);
+        got = want && i < nmine;
+        // (with fewer than 64 lanes a wave the first shares hold every track)
+        drained = share.lanes < 64u || __ballot(want && i >= nmine) != 0;
+        if (got) {
+          uint32_t idx = i, home = PHOTONS ? ln.h0 : ln.h1;
+          if (!PHOTONS && i >= ln.n1) {
+            nsp = 2;
+            idx = i - ln.n1;
+            home = ln.h2;
           }
-          stepping += nw;
+          const bool spilled = !PHOTONS && (F & kFShort) && i >= ln.n1 + ln.n2;  // an e- from the spill buffer
+          if (spilled) nsp = 1;
+          const uint32_t pos = spilled ? i - ln.n1 - ln.n2 : queue_pos(idx, home, a.cap);
+          const Queue<R> src = spilled ? short_view<R>(a, 2u) : queue_view<R>(a.qbase, a.cap, ln.cur, (uint32_t)nsp);
+          nw = src.ns[pos];
+          nt.ev = src.ev[pos];
+          nt.key = src.key[pos];
+          nt.x = src.x[pos];
+          nt.y = src.y[pos];
+          nt.z = src.z[pos];
+          nt.ux = src.ux[pos];
+          nt.uy = src.uy[pos];
+          nt.uz = src.uz[pos];
+          nt.E = src.E[pos];
+          nt.id = src.id[pos];
         }
       }
-      // batch point: few lanes still stepping
-      if (stepping == 0 || (drained ? stepping <= drain_below && __ballot(fin) != 0 : stepping <= refill_below)) {
-        // (0) e-/e+: while the queue still has tracks, interactions are
-        // sampled only once at least interact_min lanes wait for one (each
-        // sampler costs the wave one pass however few lanes use it); until
-        // then those lanes are parked: they keep their tracks and take no
-        // part in this batch.  A wave whose lanes are all parked samples
-        // them, so every wave ends (interact_min <= 64).
-        const uint32_t npend = PHOTONS ? 0u : (uint32_t)__popcll(__ballot(fin && o.pending));
-        const bool parked = !PHOTONS && !drained && npend < a.interact_min && fin && o.pending;
-        const bool done = fin && !parked;  // visits this batch finishes
-        // (1) prefetch the records of the tracks that the lanes free after
-        // this batch will take; the loads are in flight during (2)
-        // a parent that survives its interaction keeps its lane and goes on
-        // stepping in this launch while it has steps left
-        const bool will_continue = done && o.pending && parent_survives(o.process) && vs.steps < max_visit;
-        const bool want = (!has || (done && !will_continue)) && !drained && my_lane;
-        bool got = false;
-        int nsp = PHOTONS ? 0 : 1;
-        uint32_t nw = kDeadRecord;
-        Trk<R> nt;
-        if (__ballot(want) != 0) {
-          const uint32_t i = take_next(cursor, share.pool, want, chunk_lo, chunk_hi);
-          got = want && i < nmine;
-          // (with fewer than 64 lanes a wave the first shares hold every track)
-          drained = share.lanes < 64u || __ballot(want && i >= nmine) != 0;
-          if (got) {
-            uint32_t idx = i, home = PHOTONS ? h0 : h1;
-            if (!PHOTONS && i >= n1) {
-              nsp = 2;
-              idx = i - n1;
-              home = h2;
-            }
-            const bool spilled = !PHOTONS && (F & kFShort) && i >= n1 + n2;  // an e- from the spill buffer
-            if (spilled) nsp = 1;
-            const uint32_t pos = spilled ? i - n1 - n2 : queue_pos(idx, home, a.cap);
-            const Queue<R> src = spilled ? short_view<R>(a, 2u) : queue_view<R>(a.qbase, a.cap, cur, (uint32_t)nsp);
-            nw = src.ns[pos];
-            nt.ev = src.ev[pos];
-            nt.key = src.key[pos];
-            nt.x = src.x[pos];
-            nt.y = src.y[pos];
-            nt.z = src.z[pos];
-            nt.ux = src.ux[pos];
-            nt.uy = src.uy[pos];
-            nt.uz = src.uz[pos];
-            nt.E = src.E[pos];
-            nt.id = src.id[pos];
-          }
-        }
-        // (2) the interactions selected by the lanes' last steps, sampled
-        // together (one pass through each sampler the wave needs)
-        if (done && o.pending) interact<KIND, F>(env, t, o);
-        // (3) the prefetched records have arrived; waiting here, before any
-        // store of this batch is issued, keeps later uses of their fields
-        // from waiting on those stores (vector memory completes in order)
-        __builtin_amdgcn_s_waitcnt(kWaitVmem);
-        bool take = got && nw != kDeadRecord;  // dead: refused secondary or unused chunk end
-        nt.slab = (int32_t)(nw & ((1u << a.vol_bits) - 1u));
-        nt.n = nw >> a.vol_bits;
-        // a record that would index outside the tallies or the slab stack
-        // is reported, never used
-        if (take && (nt.slab >= (int32_t)a.env.n_slabs || nt.ev >= a.max_events)) {
-          atomicOr(&ctl->error, kErrCorrupt);
-          take = false;
-        }
-        // (4) commit the finished visits: reserve first, then write
-        if (__ballot(done) != 0) {
-          // secondaries into the top regions (a step commits only if all of
-          // its secondaries fit), then survivors or carried tracks
-          // e- secondaries below short_E go to the next short buffer
-          const bool s0 = shorts && done && o.nsec > 0 && o.sec[0].sp == kElectron && o.sec[0].E < a.short_E;
-          const bool s1 = shorts && done && o.nsec > 1 && o.sec[1].sp == kElectron && o.sec[1].E < a.short_E;
-          uint32_t d[3];
-#pragma unroll
-          for (int q = 0; q < 3; ++q)
-            d[q] = (done && o.nsec > 0 && o.sec[0].sp == q && !s0 ? 1u : 0u) +
-                   (done && o.nsec > 1 && o.sec[1].sp == q && !s1 ? 1u : 0u);
-          const uint32_t ds = (s0 ? 1u : 0u) + (s1 ? 1u : 0u);
-          uint32_t slot[3];
-          Take tk[3];
-          bool fits = true;
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            slot[q] = take_slots(&ctl->next_sec[q], d[q], plan.chunk[q], slo[q], shi[q], tk[q]);
-            const uint32_t lim = q == 0 ? lim0 : (q == 1 ? lim1 : lim2);
-            if (d[q] && slot_of(tk[q], slot[q] + d[q] - 1) >= lim) fits = false;
-            if (d[q] > 1 && slot_of(tk[q], slot[q]) >= lim) fits = false;
-          }
-          uint32_t slot_s = 0;
-          Take tks{0, 0, 0};
-          if (shorts) {
-            slot_s = take_slots(&ctl->next_short, ds, plan.chunk_s, sslo, sshi, tks);
-            if (ds && slot_of(tks, slot_s + ds - 1) >= plan.lim_s) fits = false;
-            if (ds > 1 && slot_of(tks, slot_s) >= plan.lim_s) fits = false;
-          }
-          const bool pending = done && o.nsec > 0;
-          const bool commit = pending && fits;
-          const bool apply_now = commit || (done && held && o.nsec == 0);
-          const bool carry = pending && !commit;  // back to the state before the last step
-          const bool alive = done && (carry ? before.slab >= 0 : t.slab >= 0);
-          const bool cont = alive && !carry && will_continue;  // stays in the lane
-          const bool keep = alive && !cont;                    // written to the next queue
-          // home slots (one counter per call: a wave may hold e- and e+)
-          uint32_t hs = 0;
-#pragma unroll
-          for (int q = PHOTONS ? 0 : 1; q < (PHOTONS ? 1 : 3); ++q) {
-            const bool mine = keep && sp == q;
-            Take th;
-            const uint32_t hx = take_slots(&ctl->next_home[q], mine ? 1u : 0u, plan.chunk[q], hlo[q], hhi[q], th);
-            if (mine) hs = slot_of(th, hx);
-          }
-          if (apply_now) {
-            sink.apply<F>(sp, t, o, before.E);
-            if (sp == 2) ++steps_p;
-            else ++steps_e;
-            made0 += d[0];
-            made1 += d[1];
-            made2 += d[2];
-            made_s += ds;
-          }
-          if (carry) ++carried_n;
-          if (done && track_live) {
-            // net change of the event's live tracks: the visited track ends
-            // or stays, committed secondaries join
-            const int delta = (alive ? 1 : 0) + (commit ? (int)(d[0] + d[1] + d[2] + ds) : 0) - 1;
-            if (delta != 0) atomicAdd(&a.live_ev[t.ev], delta);
-          }
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            if (!d[q]) continue;
-            const uint32_t lim = q == 0 ? lim0 : (q == 1 ? lim1 : lim2);
-            const Queue<R> dq = queue_view<R>(a.qbase, a.cap, nxt, (uint32_t)q);
-            uint32_t x = slot[q];
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-              if (!(k < o.nsec && o.sec[k].sp == q)) continue;
-              const uint32_t sl = slot_of(tk[q], x);
-              if (sl < lim) {
-                const uint32_t ps = (uint32_t)(a.cap - 1 - sl);
-                if (commit) {
-                  Trk<R> c;
-                  c.x = t.x;
-                  c.y = t.y;
-                  c.z = t.z;
-                  c.ux = o.sec[k].ux;
-                  c.uy = o.sec[k].uy;
-                  c.uz = o.sec[k].uz;
-                  c.E = o.sec[k].E;
-                  c.id = o.sec[k].id;
-                  c.ev = t.ev;
-                  c.key = t.key;
-                  c.n = 0;
-                  c.slab = o.slab;
-                  store_track(dq, ps, c, a.vol_bits);
-                } else {
-                  dq.ns[ps] = kDeadRecord;  // refused: the next iteration skips this slot
-                }
-              }
-              ++x;
-            }
-          }
-          if (ds) {
-            const Queue<R> sq = short_view<R>(a, nxt);
-            uint32_t x = slot_s;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-              if (!(k == 0 ? s0 : s1)) continue;
-              const uint32_t sl = slot_of(tks, x);
-              if (sl < plan.lim_s) {
-                if (commit) {
-                  Trk<R> c;
-                  c.x = t.x;
-                  c.y = t.y;
-                  c.z = t.z;
-                  c.ux = o.sec[k].ux;
-                  c.uy = o.sec[k].uy;
-                  c.uz = o.sec[k].uz;
-                  c.E = o.sec[k].E;
-                  c.id = o.sec[k].id;
-                  c.ev = t.ev;
-                  c.key = t.key;
-                  c.n = 0;
-                  c.slab = o.slab;
-                  store_track(sq, sl, c, a.vol_bits);
-                } else {
-                  sq.ns[sl] = kDeadRecord;
-                }
-              }
-              ++x;
-            }
-          }
-          if (keep) {
-            const Queue<R> dq = queue_view<R>(a.qbase, a.cap, nxt, (uint32_t)sp);
-            if (hs >= a.cap) {
-              atomicOr(&ctl->error, kErrOverflow);
-            } else {
-              if (carry) store_track(dq, hs, before, a.vol_bits);
-              else store_track(dq, hs, t, a.vol_bits);
-              if (sp == 2) ++kept_b;
-              else ++kept_a;
-            }
-          }
-          if (done) {
-            has = cont;
-            fin = false;
-            held = false;
-            o.nsec = 0;
-            o.pending = false;
-          }
-          // a continuing photon has a new energy and direction
-          if (PHOTONS && cont) photon_begin(env, t, vs.pc);
-        }
-        // (5) the freed lanes take their prefetched tracks
-        if (take) {
-          t.x = nt.x;
-          t.y = nt.y;
-          t.z = nt.z;
-          t.ux = nt.ux;
-          t.uy = nt.uy;
-          t.uz = nt.uz;
-          t.E = nt.E;
-          t.id = nt.id;
-          t.ev = nt.ev;
-          t.key = nt.key;
-          t.n = nt.n;
-          t.slab = nt.slab;
-          sp = nsp;
-          has = true;
-          visit_begin<KIND>(env, sp, t, vs);
-          world_ready = false;
-          if (sp == 2) ++visits_p;
-          else ++visits_e;
-        }
-        if (__ballot(has) == 0) {
-          if (drained) break;
-          continue;
-        }
-        // tracks just taken that start in the world wait for a world pass
-        if constexpr (GEO == 1)
-          world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == env.nav.n_boxes;
+      // (2) the interactions selected by the lanes' last steps, sampled
+      // together (one pass through each sampler the wave needs)
+      if constexpr (!kTurns) {
+        ux0 = t.ux;
+        uy0 = t.uy;
+        uz0 = t.uz;
       }
-
-      // one step of every lane inside a visit
-      if (has && !fin && !world_wait) {
-        before = t;
-        const double e0 = t.E;
-        fin = visit_step<KIND, R, GEO, F>(env, sp, vs, t, o, max_visit, world_ready ? &world_pre : nullptr);
-        world_ready = false;
-        held = o.pending;
-        if (!held) {
+      if (done && o.pending) interact<KIND, F>(env, t, o);
+      // (3) the prefetched records have arrived; waiting here, before any
+      // store of this batch is issued, keeps later uses of their fields
+      // from waiting on those stores (vector memory completes in order)
+      __builtin_amdgcn_s_waitcnt(kWaitVmem);
+      bool take = got && nw != kDeadRecord;  // dead: refused secondary or unused chunk end
+      nt.slab = (int32_t)(nw & ((1u << a.vol_bits) - 1u));
+      nt.n = nw >> a.vol_bits;
+      // a record that would index outside the tallies or the slab stack
+      // is reported, never used
+      if (take && (nt.slab >= (int32_t)a.env.n_slabs || nt.ev >= a.max_events)) {
+        atomicOr(&ctl->error, kErrCorrupt);
+        take = false;
+      }
+      // (4) commit the finished visits: reserve first, then write
+      if (__ballot(done) != 0) {
+        // secondaries into the top regions (a step commits only if all of
+        // its secondaries fit), then survivors or carried tracks
+        // e- secondaries below short_E go to the next short buffer
+        const bool s0 = shorts && done && o.nsec > 0 && o.sec[0].sp == kElectron && o.sec[0].E < a.short_E;
+        const bool s1 = shorts && done && o.nsec > 1 && o.sec[1].sp == kElectron && o.sec[1].E < a.short_E;
+        const bool in0 = done && o.nsec > 0 && !s0, in1 = done && o.nsec > 1 && !s1;  // to the queues
+        const uint32_t da = (in0 && o.sec[0].sp == kSecA ? 1u : 0u) + (in1 && o.sec[1].sp == kSecA ? 1u : 0u);
+        const uint32_t db = (in0 && o.sec[0].sp == kSecB ? 1u : 0u) + (in1 && o.sec[1].sp == kSecB ? 1u : 0u);
+        const uint32_t ds = (s0 ? 1u : 0u) + (s1 ? 1u : 0u);
+        // a home slot for every survivor that leaves the lane
+        const bool leave = done && t.slab >= 0 && !will_continue;
+        Take ta = ask(rg, kNextSec + kSecA, da), tb = ask(rg, kNextSec + kSecB, db);
+        Take th = ask(rg, kNextHome + (PHOTONS ? 0 : 1), leave && sp != 2 ? 1u : 0u);
+        Take tp{0, 0, 0, 0, 0}, ts{0, 0, 0, 0, 0};
+        if constexpr (!PHOTONS) tp = ask(rg, kNextHome + 2, leave && sp == 2 ? 1u : 0u);
+        if (shorts) ts = ask(rg, kNextShort, ds);
+        if constexpr (PHOTONS) {
+          if constexpr (kShort) {
+            const Ask asks[4] = {{kNextSec + kSecA, plan.chunk[kSecA], &ta}, {kNextSec + kSecB, plan.chunk[kSecB], &tb},
+                                 {kNextHome, plan.chunk[0], &th}, {kNextShort, plan.chunk_s, &ts}};
+            serve(ctl, rg, asks);
+          } else {
+            const Ask asks[3] = {{kNextSec + kSecA, plan.chunk[kSecA], &ta}, {kNextSec + kSecB, plan.chunk[kSecB], &tb},
+                                 {kNextHome, plan.chunk[0], &th}};
+            serve(ctl, rg, asks);
+          }
+        } else if constexpr (kShort) {
+          const Ask asks[5] = {{kNextSec + kSecA, plan.chunk[kSecA], &ta}, {kNextSec + kSecB, plan.chunk[kSecB], &tb},
+                               {kNextHome + 1, plan.chunk[1], &th}, {kNextHome + 2, plan.chunk[2], &tp},
+                               {kNextShort, plan.chunk_s, &ts}};
+          serve(ctl, rg, asks);
+        } else {
+          const Ask asks[4] = {{kNextSec + kSecA, plan.chunk[kSecA], &ta}, {kNextSec + kSecB, plan.chunk[kSecB], &tb},
+                               {kNextHome + 1, plan.chunk[1], &th}, {kNextHome + 2, plan.chunk[2], &tp}};
+          serve(ctl, rg, asks);
+        }
+        const uint32_t lim_a = plan.lim[kSecA], lim_b = plan.lim[kSecB];
+        bool fits = !(da && (ta.slot(da - 1) >= lim_a || ta.slot(0) >= lim_a)) &&
+                    !(db && (tb.slot(db - 1) >= lim_b || tb.slot(0) >= lim_b));
+        if (shorts && ds && (ts.slot(ds - 1) >= plan.lim_s || ts.slot(0) >= plan.lim_s)) fits = false;
+        const bool pending = done && o.nsec > 0;
+        const bool commit = pending && fits;
+        const bool carry = pending && !fits;  // back to the state before the last step
+        const bool cont = done && t.slab >= 0 && !carry && will_continue;  // stays in the lane
+        const bool keep = leave || carry;                                  // written to the next queue
+        uint32_t hs = sp == 2 ? tp.slot(0) : th.slot(0);
+        // carried tracks that were not to leave still need a home slot
+        const bool late = carry && !leave;
+        if (__ballot(late) != 0) {
+          Take lh = ask(rg, kNextHome + (PHOTONS ? 0 : 1), late && sp != 2 ? 1u : 0u);
+          Take lp{0, 0, 0, 0, 0};
+          if constexpr (PHOTONS) {
+            const Ask asks[1] = {{kNextHome, plan.chunk[0], &lh}};
+            serve(ctl, rg, asks);
+          } else {
+            lp = ask(rg, kNextHome + 2, late && sp == 2 ? 1u : 0u);
+            const Ask asks[2] = {{kNextHome + 1, plan.chunk[1], &lh}, {kNextHome + 2, plan.chunk[2], &lp}};
+            serve(ctl, rg, asks);
+          }
+          if (late) hs = sp == 2 ? lp.slot(0) : lh.slot(0);
+        }
+        if (commit || (done && held && o.nsec == 0)) {
           sink.apply<F>(sp, t, o, e0);
           if (sp == 2) ++steps_p;
           else ++steps_e;
+          made_a += da;
+          made_b += db;
+          made_s += ds;
         }
+        if (carry) ++carried_n;
+        if (done && track_live) {
+          // net change of the event's live tracks: the visited track ends
+          // or stays, committed secondaries join
+          const int delta = (keep || cont ? 1 : 0) + (commit ? (int)(da + db + ds) : 0) - 1;
+          if (delta != 0) atomicAdd(&a.live_ev[t.ev], delta);
+        }
+        // secondary number k to slot sl of its queue's top region (or, to
+        // the short buffer, from the bottom); a refused one marks its slot
+        // dead for the next iteration
+        auto put = [&](const Queue<R>& dq, const Sec<R>& sec, uint32_t ps) {
+          if (commit) {
+            Trk<R> c;
+            c.x = t.x;
+            c.y = t.y;
+            c.z = t.z;
+            c.ux = sec.ux;
+            c.uy = sec.uy;
+            c.uz = sec.uz;
+            c.E = sec.E;
+            c.id = sec.id;
+            c.ev = t.ev;
+            c.key = t.key;
+            c.n = 0;
+            c.slab = o.slab;
+            store_track(dq, ps, c, a.vol_bits);
+          } else {
+            dq.ns[ps] = kDeadRecord;
+          }
+        };
+        auto put_queue = [&](int q, uint32_t d, const Take& tk, uint32_t lim) {
+          if (!d) return;
+          const Queue<R> dq = queue_view<R>(a.qbase, a.cap, nxt, (uint32_t)q);
+          const bool first = in0 && o.sec[0].sp == q;
+          const uint32_t sl = tk.slot(0);
+          if (sl < lim) put(dq, first ? o.sec[0] : o.sec[1], (uint32_t)(a.cap - 1 - sl));
+          if (d > 1) {
+            const uint32_t s2 = tk.slot(1);
+            if (s2 < lim) put(dq, o.sec[1], (uint32_t)(a.cap - 1 - s2));
+          }
+        };
+        put_queue(kSecA, da, ta, lim_a);
+        put_queue(kSecB, db, tb, lim_b);
+        if (kShort && ds) {
+          const Queue<R> sq = short_view<R>(a, nxt);
+          const uint32_t sl = ts.slot(0);
+          if (sl < plan.lim_s) put(sq, s0 ? o.sec[0] : o.sec[1], sl);
+          if (ds > 1) {
+            const uint32_t s2 = ts.slot(1);
+            if (s2 < plan.lim_s) put(sq, o.sec[1], s2);
+          }
+        }
+        if (keep) {
+          const Queue<R> dq = queue_view<R>(a.qbase, a.cap, nxt, (uint32_t)sp);
+          if (hs >= a.cap) {
+            atomicOr(&ctl->error, kErrOverflow);
+          } else {
+            Trk<R> w = t;
+            if (carry) {
+              w.x = x0;
+              w.y = y0;
+              w.z = z0;
+              w.E = e0;
+              w.ux = ux0;
+              w.uy = uy0;
+              w.uz = uz0;
+              w.n = t.n - 1;
+              w.slab = o.slab;
+            }
+            store_track(dq, hs, w, a.vol_bits);
+            if (sp == 2) ++kept_b;
+            else ++kept_a;
+          }
+        }
+        if (done) {
+          has = cont;
+          fin = false;
+          held = false;
+          o.nsec = 0;
+          o.pending = false;
+        }
+        // a continuing photon has a new energy and direction
+        if (PHOTONS && cont) photon_begin(env, t, vs.pc);
       }
+      // (5) the freed lanes take their prefetched tracks
+      if (take) {
+        t.x = nt.x;
+        t.y = nt.y;
+        t.z = nt.z;
+        t.ux = nt.ux;
+        t.uy = nt.uy;
+        t.uz = nt.uz;
+        t.E = nt.E;
+        t.id = nt.id;
+        t.ev = nt.ev;
+        t.key = nt.key;
+        t.n = nt.n;
+        t.slab = nt.slab;
+        sp = nsp;
+        has = true;
+        visit_begin<KIND>(env, sp, t, vs);
+        world_ready = false;
+        if (sp == 2) ++visits_p;
+        else ++visits_e;
+      }
+      if (__ballot(has) == 0) {
+        if (drained) break;
+        continue;
+      }
+      // tracks just taken that start in the world wait for a world pass
+      if constexpr (GEO == 1)
+        world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == env.nav.n_boxes;
     }
 
-    sink.flush();
+    // one step of every lane inside a visit
+    if (has && !fin && !world_wait) {
+      x0 = t.x;
+      y0 = t.y;
+      z0 = t.z;
+      e0 = t.E;
+      if constexpr (kTurns) {
+        ux0 = t.ux;
+        uy0 = t.uy;
+        uz0 = t.uz;
+      }
+      fin = visit_step<KIND, R, GEO, F>(env, sp, vs, t, o, max_visit, world_ready ? &world_pre : nullptr);
+      world_ready = false;
+      held = o.pending;
+      if (!held) {
+        sink.apply<F>(sp, t, o, e0);
+        if (sp == 2) ++steps_p;
+        else ++steps_e;
+      }
+    }
+  }
+
+  sink.flush();
+  constexpr int kOwn = PHOTONS ? 0 : 1;
+  count(ln.cnt, kAddSteps + kOwn, steps_e);
+  count(ln.cnt, kAddVisits + kOwn, visits_e);
+  count(ln.cnt, kAddKept + kOwn, kept_a);
+  if constexpr (!PHOTONS) {
+    count(ln.cnt, kAddSteps + 2, steps_p);
+    count(ln.cnt, kAddVisits + 2, visits_p);
+    count(ln.cnt, kAddKept + 2, kept_b);
+  }
+  count(ln.cnt, kAddMade + kSecA, made_a + (kSecA == kElectron ? made_s : 0u));
+  count(ln.cnt, kAddMade + kSecB, made_b + (kSecB == kElectron ? made_s : 0u));
+  count(ln.cnt, kAddMadeBy + kOwn, made_a + made_b + made_s);
+  count(ln.cnt, kAddCarried, carried_n);
+  if constexpr (kShort) count(ln.cnt, kAddMadeShort, made_s);
+}
+
+// The last block of an iteration to end folds the tallies into the totals
+// and makes the next queues the current ones.  Wave 0 of that block does it,
+// a counter to a lane: every counter is fetched and cleared in one exchange
+// each (they live at the memory side, some microseconds a round trip; one
+// after another they took 9 us of every iteration).
+template <bool SHORT>
+__device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& ln) {
+  const uint32_t lane = __lane_id();
+  uint32_t app = 0;
+  unsigned long long add = 0;
+  if (lane < kNextCounters) app = atomicExch(&ctl->next[lane], 0u);
+  if (lane < kAdds) add = atomicExch(&ctl->add[lane], 0ull);
+  auto next_of = [&](int c) { return (uint32_t)__builtin_amdgcn_readlane((int)app, c); };
+  auto add_of = [&](int k) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)add, k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(add >> 32), k);
+    return (unsigned long long)lo | ((unsigned long long)hi << 32);
+  };
+  const uint32_t srv = SHORT ? (uint32_t)add_of(kAddMadeShort) : 0u;
+  uint32_t real[3], live = srv;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    real[q] = (uint32_t)(add_of(kAddMade + q) + add_of(kAddKept + q)) - (q == 1 ? srv : 0u);
+    live += real[q];
+  }
+  uint32_t home[3], sec[3];
+  unsigned long long tot[kAdds];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    home[q] = next_of(kNextHome + q);
+    sec[q] = next_of(kNextSec + q);
+  }
+#pragma unroll
+  for (int k = 0; k < kAdds; ++k) tot[k] = add_of(k);
+  const uint32_t shorts = SHORT ? next_of(kNextShort) : 0u;
+  const unsigned long long commits = tot[kAddSteps] + tot[kAddSteps + 1] + tot[kAddSteps + 2];
+  const unsigned long long carried = tot[kAddCarried];
+  if (lane != 0) return;
+  const uint32_t r0 = ctl->n_real[0], r1 = ctl->n_real[1] + (SHORT ? ctl->n_short_real : 0u), r2 = ctl->n_real[2];
+  if (a.flags & kFlagProfile) {
+    if (ctl->iteration < a.profile_cap) {
+      a.profile[(size_t)ctl->iteration * 3 + 0] = r0;
+      a.profile[(size_t)ctl->iteration * 3 + 1] = r1;
+      a.profile[(size_t)ctl->iteration * 3 + 2] = r2;
+    }
+  }
+  if (r0 + r1 + r2 > 0) ctl->iteration += 1;
+  if (carried > 0 && commits == 0) atomicOr(&ctl->error, kErrStall);  // nothing can move: queues too small
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    // with no live track left the dead slots need no visit
+    ctl->n_home[q] = live ? home[q] : 0u;
+    ctl->n_sec[q] = live ? (sec[q] < ln.plan.lim[q] ? sec[q] : ln.plan.lim[q]) : 0u;
+    ctl->n_real[q] = real[q];
+    const uint32_t all = real[q] + (q == 1 ? srv : 0u);
+    ctl->peak[q] = all > ctl->peak[q] ? all : ctl->peak[q];
+    ctl->steps[q] += tot[kAddSteps + q];
+    ctl->visits[q] += tot[kAddVisits + q];
+    ctl->created[q] += tot[kAddMade + q];
+  }
+  ctl->made_by[0] += tot[kAddMadeBy];
+  ctl->made_by[1] += tot[kAddMadeBy + 1];
+  ctl->deferred += carried;
+  if constexpr (SHORT) {
+    // the next short buffer becomes the current one
+    ctl->n_short = live ? (shorts < ln.plan.lim_s ? shorts : ln.plan.lim_s) : 0u;
+    ctl->n_short_real = srv;
+    ctl->steps_s += tot[kAddStepsShort];
+  }
+  ctl->live = live;
+  ctl->cursor[0] = 0;
+  ctl->cursor[1] = 0;
+  ctl->cur = ln.cur ^ 1u;
+  ctl->blocks_done = 0;
+}
+
+// One iteration: every track of the current queues is visited once.  The
+// two species' loops do not depend on each other within an iteration (both
+// read the current queues and append to the next), so one launch runs both:
+// the waves are dealt to the species in proportion to their tracks, and a
+// wave whose species is used up goes on with the other one, so the tail of
+// one overlaps the other.  `which` names the species of the launch: both, or
+// one after the other in a launch each (per-kernel timing, or tables that
+// would cost resident blocks if both were staged); the launch of the e-/e+
+// closes the iteration.
+// Measured against two launches an iteration (with the counters' round trips
+// one after another): 32 x 1 GeV 3.4 -> 2.2 ms, 500 x 2 GeV 8.1 -> 5.5 ms,
+// 10^4 x 10 GeV 59.2 -> 55.1 ms, 1501 mixed-species events in a field, mixed
+// form 28.6 -> 21.7 ms.  All waves on photons first, then on e-/e+, instead
+// of dealt to both from the start: 10^4 x 10 GeV 56.9 ms, 2500 mixed-species
+// events in a field 39.9 instead of 37.8 ms.
+template <class R, int GEO, int F>
+__global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KArgs a, uint32_t which) {
+  extern __shared__ double lds_words[];
+  __shared__ unsigned long long cnt[kAdds];
+  Ctl* ctl = a.ctl;
+  constexpr bool kShort = (F & kFShort) != 0;
+  Launch ln;
+  ln.cnt = cnt;
+  ln.cur = ctl->cur;
+  ln.h0 = ctl->n_home[0];
+  ln.h1 = ctl->n_home[1];
+  ln.h2 = ctl->n_home[2];
+  ln.n0 = ln.h0 + ctl->n_sec[0];
+  ln.n1 = ln.h1 + ctl->n_sec[1];
+  ln.n2 = ln.h2 + ctl->n_sec[2];
+  // the e-/e+ loop also takes the tracks the short launch spilled
+  const uint32_t np_raw = kShort ? ctl->next[kNextSpill] : 0u;
+  ln.np = (uint64_t)np_raw < a.cap_p ? np_raw : (uint32_t)a.cap_p;
+  // secondary slots per species that leave room for all survivors
+  ln.plan = append_plan<kShort>(a, ln.n0, ln.n1, ln.n2, kShort ? ctl->n_short : 0u);
+  const uint32_t ng = which & kPhotons ? ln.n0 : 0u, nl = which & kLeptons ? ln.n1 + ln.n2 + ln.np : 0u;
+  const uint32_t waves = gridDim.x * (kBlock / 64);
+  uint32_t wg = (uint32_t)((uint64_t)waves * ng / ((uint64_t)ng + nl + (ng + nl == 0u)));
+  if (ng) wg = wg < 1u ? 1u : wg;
+  if (nl) wg = wg < waves ? wg : waves - 1u;
+  // consecutive waves of a species go to different blocks (and so CUs)
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+  const WaveShare sg = wave_share(ng, w, wg ? wg : 1u);
+  const WaveShare sl = wave_share(nl, w - wg, waves > wg ? waves - wg : 1u);
+  bool work = false;
+  for (uint32_t k = 0; k < kBlock / 64; ++k) {
+    const uint32_t wk = k * gridDim.x + blockIdx.x;
+    work = work || (wk < wg ? (uint64_t)wk * sg.lanes < ng : (uint64_t)(wk - wg) * sl.lanes < nl);
+  }
+  if (work && ctl->error == 0) {
+    clear_counts(cnt);
+    const StepEnv<R> env = stage<R, GEO>(a, reinterpret_cast<char*>(lds_words), which);
+    Ranges rg{};
+    const bool own_g = w < wg;
+#pragma unroll 1
+    for (int turn = 0; turn < 2; ++turn) {
+      const bool photons = own_g == (turn == 0);
+      if (turn == 1 && (photons ? ng == 0u || sg.lanes < 64u : nl == 0u || sl.lanes < 64u)) break;
+      if (photons) {
+        const WaveShare s = turn == 0 ? sg : WaveShare{64u, sg.pool, sg.pool};
+        visit_loop<true, R, GEO, F>(a, ctl, env, ln, s, rg);
+      } else {
+        const WaveShare s = turn == 0 ? sl : WaveShare{64u, sl.pool, sl.pool};
+        visit_loop<false, R, GEO, F>(a, ctl, env, ln, s, rg);
+      }
+    }
     // unused ends of the wave's append ranges hold no track
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const Queue<R> dq = queue_view<R>(a.qbase, a.cap, nxt, (uint32_t)q);
-      const uint32_t lim = q == 0 ? lim0 : (q == 1 ? lim1 : lim2);
-      const uint32_t send = shi[q] < lim ? shi[q] : lim;
-      for (uint32_t x = slo[q] + __lane_id(); x < send; x += 64) dq.ns[a.cap - 1 - x] = kDeadRecord;
-      for (uint32_t x = hlo[q] + __lane_id(); x < hhi[q]; x += 64) {
+      const Queue<R> dq = queue_view<R>(a.qbase, a.cap, ln.cur ^ 1u, (uint32_t)q);
+      const uint32_t lim = ln.plan.lim[q];
+      const uint32_t send = rg.hi[kNextSec + q] < lim ? rg.hi[kNextSec + q] : lim;
+      for (uint32_t x = rg.lo[kNextSec + q] + __lane_id(); x < send; x += 64) dq.ns[a.cap - 1 - x] = kDeadRecord;
+      for (uint32_t x = rg.lo[kNextHome + q] + __lane_id(); x < rg.hi[kNextHome + q]; x += 64) {
         if (x < a.cap) dq.ns[x] = kDeadRecord;
       }
     }
-    if (shorts) {
-      const Queue<R> sq = short_view<R>(a, nxt);
-      const uint32_t send = sshi < plan.lim_s ? sshi : plan.lim_s;
-      for (uint32_t x = sslo + __lane_id(); x < send; x += 64) sq.ns[x] = kDeadRecord;
+    if (kShort && a.cap_s) {
+      const Queue<R> sq = short_view<R>(a, ln.cur ^ 1u);
+      const uint32_t send = rg.hi[kNextShort] < ln.plan.lim_s ? rg.hi[kNextShort] : ln.plan.lim_s;
+      for (uint32_t x = rg.lo[kNextShort] + __lane_id(); x < send; x += 64) sq.ns[x] = kDeadRecord;
     }
-    // statistics and per-launch progress
-    if (PHOTONS) {
-      wave_count(&ctl->steps[0], steps_e);
-      wave_count(&ctl->visits[0], visits_e);
-    } else {
-      wave_count(&ctl->steps[1], steps_e);
-      wave_count(&ctl->steps[2], steps_p);
-      wave_count(&ctl->visits[1], visits_e);
-      wave_count(&ctl->visits[2], visits_p);
-    }
-    wave_count(&ctl->deferred, carried_n);
-    wave_count(&ctl->created[0], made0);
-    wave_count(&ctl->created[1], made1 + made_s);
-    wave_count(&ctl->created[2], made2);
-    wave_count(&ctl->made_by[PHOTONS ? 0 : 1], made0 + made1 + made2 + made_s);
-    if (shorts) wave_count(&ctl->next_short_real, made_s);
-    wave_count(&ctl->next_real[0], made0 + (PHOTONS ? kept_a : 0u));
-    wave_count(&ctl->next_real[1], made1 + (PHOTONS ? 0u : kept_a));
-    wave_count(&ctl->next_real[2], made2 + kept_b);
-    const uint32_t c = wave_sum(steps_e + steps_p), k = wave_sum(carried_n);
-    if (__lane_id() == 0) {
-      if (c) atomicAdd(&ctl->commits, c);
-      if (k) atomicAdd(&ctl->carried, k);
-    }
+    publish_counts(ctl, cnt);
   }
 
-  if (PHOTONS) return;
-
-  // the last block of the e-/e+ launch publishes the next iteration (the
-  // photon launch of this iteration finished before this launch started)
-  __shared__ uint32_t last;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    last = atomicAdd(&ctl->blocks_done, 1u) == gridDim.x - 1;
-  }
-  __syncthreads();
-  if (last && threadIdx.x == 0) {
-    __threadfence();
-    const uint32_t r0 = ctl->n_real[0], r1 = ctl->n_real[1] + (kShort ? ctl->n_short_real : 0u), r2 = ctl->n_real[2];
-    if (a.flags & kFlagProfile) {
-      if (ctl->iteration < a.profile_cap) {
-        a.profile[(size_t)ctl->iteration * 3 + 0] = r0;
-        a.profile[(size_t)ctl->iteration * 3 + 1] = r1;
-        a.profile[(size_t)ctl->iteration * 3 + 2] = r2;
-      }
-    }
-    if (r0 + r1 + r2 > 0) ctl->iteration += 1;
-    const uint32_t commits = atomicAdd(&ctl->commits, 0u), carried = atomicAdd(&ctl->carried, 0u);
-    if (carried > 0 && commits == 0) ctl->error |= kErrStall;  // nothing can move: queues too small
-    const uint32_t srv = kShort ? atomicAdd(&ctl->next_short_real, 0u) : 0u;
-    uint32_t live = srv;
-    for (int q = 0; q < 3; ++q) live += atomicAdd(&ctl->next_real[q], 0u);
-    const Plan plan = append_plan<kShort>(a, n0, n1, n2, ns);
-    for (int q = 0; q < 3; ++q) {
-      const uint32_t lim = plan.lim[q];
-      const uint32_t hv = atomicAdd(&ctl->next_home[q], 0u);
-      uint32_t sv = atomicAdd(&ctl->next_sec[q], 0u);
-      sv = sv < lim ? sv : lim;
-      const uint32_t rv = atomicAdd(&ctl->next_real[q], 0u);
-      // with no live track left the dead slots need no visit
-      ctl->n_home[q] = live ? hv : 0u;
-      ctl->n_sec[q] = live ? sv : 0u;
-      ctl->n_real[q] = rv;
-      ctl->next_home[q] = 0;
-      ctl->next_sec[q] = 0;
-      ctl->next_real[q] = 0;
-      ctl->peak[q] = rv > ctl->peak[q] ? rv : ctl->peak[q];
-    }
-    if constexpr (kShort) {
-      // the next short buffer becomes the current one
-      const uint32_t sv = atomicAdd(&ctl->next_short, 0u);
-      ctl->n_short = live ? (sv < plan.lim_s ? sv : plan.lim_s) : 0u;
-      ctl->n_short_real = srv;
-      ctl->next_short = 0;
-      ctl->next_short_real = 0;
-      ctl->n_spill = 0;
-      ctl->cursor_s = 0;
-      ctl->peak[1] = ctl->n_real[1] + srv > ctl->peak[1] ? ctl->n_real[1] + srv : ctl->peak[1];
-    }
-    ctl->live = live;
-    ctl->commits = 0;
-    ctl->carried = 0;
-    ctl->cursor[0] = 0;
-    ctl->cursor[1] = 0;
-    ctl->cur = cur ^ 1u;
-    ctl->blocks_done = 0;
-    __threadfence();
-  }
+  if (!(which & kLeptons)) return;
+  // The block's increments are performed (every atomic at the memory side)
+  // before its ticket is counted, so the block that draws the last ticket
+  // sees them all; the records themselves are read by the next launch.
+  if (threadIdx.x >= 64) return;
+  __builtin_amdgcn_s_waitcnt(kWaitVmem);
+  uint32_t ticket = 0;
+  if (threadIdx.x == 0) ticket = atomicAdd(&ctl->blocks_done, 1u);
+  ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)ticket);
+  if (ticket == gridDim.x - 1) close_iteration<kShort>(a, ctl, ln);
 }
 
 // Short electrons.  Most e- secondaries of a shower are slow (Compton and
@@ -938,13 +1059,15 @@ template <class R, int GEO, int F>
 __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KArgs a) {
   extern __shared__ double lds_words[];
   char* lds = reinterpret_cast<char*>(lds_words);
+  __shared__ unsigned long long cnt[kAdds];
   Ctl* ctl = a.ctl;
   const uint32_t cur = ctl->cur;
   const uint32_t ns = ctl->n_short;
   if (blockIdx.x >= (ns + kBlock - 1) / kBlock || ctl->error != 0) return;
   const uint32_t n0 = ctl->n_home[0] + ctl->n_sec[0], n1 = ctl->n_home[1] + ctl->n_sec[1];
   const uint32_t n2 = ctl->n_home[2] + ctl->n_sec[2];
-  const StepEnv<R> env = stage<R, GEO>(a, lds, false);
+  clear_counts(cnt);
+  const StepEnv<R> env = stage<R, GEO>(a, lds, kLeptons);
   const Plan plan = append_plan<true>(a, n0, n1, n2, ns);
   DevSink sink{a.edep, a.ledger, ctl, a.log, a.log_cap, a.env.n_slabs,
                (a.flags & kFlagFullLedger) != 0, (a.flags & kFlagSteplog) != 0, 0, 0.0,
@@ -953,8 +1076,8 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   const Queue<R> src = short_view<R>(a, cur);
   const Queue<R> spill = short_view<R>(a, 2u);
   const Queue<R> dst = queue_view<R>(a.qbase, a.cap, cur ^ 1u, (uint32_t)kElectron);
-  // wave-private append ranges (uniform): next e- home, spill buffer
-  uint32_t hlo = 0, hhi = 0, plo = 0, phi = 0;
+  // wave-private append ranges: next e- home, spill buffer
+  Ranges rg{};
   // spill appends: all waves' unused chunk ends fit in the spill buffer's
   // room beyond cap_s (at most ns <= cap_s tracks spill)
   uint32_t chunk_p = plan.chunk[1] < 64u ? plan.chunk[1] : 64u;
@@ -1011,11 +1134,11 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
         if (track_live && !alive) atomicAdd(&a.live_ev[t.ev], -1);
       }
     }
-    Take th, tp;
-    const uint32_t hx = take_slots(&ctl->next_home[1], alive ? 1u : 0u, plan.chunk[1], hlo, hhi, th);
-    const uint32_t px = take_slots(&ctl->n_spill, to_spill ? 1u : 0u, chunk_p, plo, phi, tp);
+    Take th = ask(rg, kNextHome + 1, alive ? 1u : 0u), tp = ask(rg, kNextSpill, to_spill ? 1u : 0u);
+    const Ask asks[2] = {{kNextHome + 1, plan.chunk[1], &th}, {kNextSpill, chunk_p, &tp}};
+    serve(ctl, rg, asks);
     if (alive) {
-      const uint32_t hs = slot_of(th, hx);
+      const uint32_t hs = th.slot(0);
       if (hs >= a.cap) {
         atomicOr(&ctl->error, kErrOverflow);
       } else {
@@ -1024,7 +1147,7 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
       }
     }
     if (to_spill) {
-      const uint32_t ps = slot_of(tp, px);
+      const uint32_t ps = tp.slot(0);
       if (ps >= a.cap_p) atomicOr(&ctl->error, kErrOverflow);
       else store_track(spill, ps, first, a.vol_bits);
     }
@@ -1032,18 +1155,17 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
     w = wn;
   }
   sink.flush();
-  for (uint32_t x = hlo + __lane_id(); x < hhi; x += 64) {
+  for (uint32_t x = rg.lo[kNextHome + 1] + __lane_id(); x < rg.hi[kNextHome + 1]; x += 64) {
     if (x < a.cap) dst.ns[x] = kDeadRecord;
   }
-  for (uint32_t x = plo + __lane_id(); x < phi; x += 64) {
+  for (uint32_t x = rg.lo[kNextSpill] + __lane_id(); x < rg.hi[kNextSpill]; x += 64) {
     if (x < a.cap_p) spill.ns[x] = kDeadRecord;
   }
-  wave_count(&ctl->steps[1], steps);
-  wave_count(&ctl->steps_s, steps);
-  wave_count(&ctl->visits[1], loads);
-  wave_count(&ctl->next_real[1], kept);
-  const uint32_t c = wave_sum(steps);
-  if (__lane_id() == 0 && c) atomicAdd(&ctl->commits, c);
+  count(cnt, kAddSteps + 1, steps);
+  count(cnt, kAddStepsShort, steps);
+  count(cnt, kAddVisits + 1, loads);
+  count(cnt, kAddKept + 1, kept);
+  publish_counts(ctl, cnt);
 }
 
 #ifndef EMS_SLAB_F32_TU
@@ -1157,26 +1279,23 @@ __global__ void k_census(KArgs a) {
 
 #endif  // EMS_SLAB_F32_TU
 
-// Kernel variants: the optional parts each kernel is built with.  The
-// e-/e+ kernel of a slab stack comes without any, with the field and the
-// records (mixed-species runs in a field, the offload server) or with all;
-// the photon kernels and the box-geometry e-/e+ kernels without any or with
-// all.  A context launches the smallest variant that covers its
-// configuration (KArgs::feat_g, feat_l).
-template <bool PHOTONS, class R, int GEO>
+// Kernel variants: the optional parts each kernel is built with: none, in a
+// slab stack the field and the records (mixed-species runs in a field, the
+// offload server), or all.  A context launches the smallest variant that
+// covers its configuration (KArgs::feat).
+template <class R, int GEO>
 const void* visit_fn(uint32_t feat) {
-  if (feat == 0) return reinterpret_cast<const void*>(&k_visit<PHOTONS, R, GEO, 0>);
-  if (feat == kFShort) return reinterpret_cast<const void*>(&k_visit<PHOTONS, R, GEO, kFShort>);
-  if constexpr (!PHOTONS && GEO == 0) {
-    if (feat == (kFField | kFRecord))
-      return reinterpret_cast<const void*>(&k_visit<PHOTONS, R, GEO, kFField | kFRecord>);
+  if (feat == 0) return reinterpret_cast<const void*>(&k_visit<R, GEO, 0>);
+  if (feat == kFShort) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFShort>);
+  if constexpr (GEO == 0) {
+    if (feat == (kFField | kFRecord)) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFField | kFRecord>);
     if (feat == (kFField | kFRecord | kFShort))
-      return reinterpret_cast<const void*>(&k_visit<PHOTONS, R, GEO, kFField | kFRecord | kFShort>);
+      return reinterpret_cast<const void*>(&k_visit<R, GEO, kFField | kFRecord | kFShort>);
   }
-  if (feat == (kFAll & ~kFShort)) return reinterpret_cast<const void*>(&k_visit<PHOTONS, R, GEO, kFAll & ~kFShort>);
-  return reinterpret_cast<const void*>(&k_visit<PHOTONS, R, GEO, kFAll>);
+  if (feat == (kFAll & ~kFShort)) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFAll & ~kFShort>);
+  return reinterpret_cast<const void*>(&k_visit<R, GEO, kFAll>);
 }
-// the short launch takes the e-/e+ launch's optional parts (its own work is
+// the short launch takes the visit launch's optional parts (its own work is
 // the short path, so the routing bit does not apply to it)
 template <class R, int GEO>
 const void* short_fn(uint32_t feat) {
@@ -1187,33 +1306,37 @@ const void* short_fn(uint32_t feat) {
   }
   return reinterpret_cast<const void*>(&k_short<R, GEO, kFAll>);
 }
+// the visit kernel, or the short launch's
 template <class R, int GEO>
-const void* kernel_of(const KArgs& a, int which) {
-  return which == 0 ? visit_fn<true, R, GEO>(a.feat_g)
-                    : (which == 1 ? visit_fn<false, R, GEO>(a.feat_l) : short_fn<R, GEO>(a.feat_l));
+const void* kernel_of(const KArgs& a, bool shorts) {
+  return shorts ? short_fn<R, GEO>(a.feat) : visit_fn<R, GEO>(a.feat);
 }
 #ifdef EMS_SLAB_F32_TU
-const void* kernel_of_slab_f32(const KArgs& a, int which) { return kernel_of<float, 0>(a, which); }
+const void* kernel_of_slab_f32(const KArgs& a, bool shorts) { return kernel_of<float, 0>(a, shorts); }
 #else
 // The mixed-form kernels of the slab stack come from a translation unit of
 // their own (ems_kernels_slab_f32.hip), built with another instruction
 // scheduler (see build.py).
-const void* kernel_of_slab_f32(const KArgs& a, int which);
-// which: 0 photon, 1 e-/e+, 2 short-electron launch
-const void* kernel_for(const KArgs& a, int which) {
-  if (a.geo == 1) return a.precision ? kernel_of<float, 1>(a, which) : kernel_of<double, 1>(a, which);
-  return a.precision ? kernel_of_slab_f32(a, which) : kernel_of<double, 0>(a, which);
+const void* kernel_of_slab_f32(const KArgs& a, bool shorts);
+const void* kernel_for(const KArgs& a, bool shorts) {
+  if (a.geo == 1) return a.precision ? kernel_of<float, 1>(a, shorts) : kernel_of<double, 1>(a, shorts);
+  return a.precision ? kernel_of_slab_f32(a, shorts) : kernel_of<double, 0>(a, shorts);
 }
-hipError_t launch_kernel(const KArgs& a, int which, uint32_t blocks, hipStream_t s) {
+// LDS of a visit launch of the species `which`
+uint32_t visit_lds(const KArgs& a, uint32_t which) {
+  return which == kPhotons ? a.lds_g : (which == kLeptons ? a.lds_l : a.lds_gl);
+}
+// one iteration is the short-electron launch (with short buffers), then one
+// visit launch of both species or one of each
+hipError_t launch_short(const KArgs& a, uint32_t blocks, hipStream_t s) {
   KArgs arg = a;
   void* args[] = {&arg};
-  return hipLaunchKernel(kernel_for(a, which), dim3(blocks), dim3(kBlock), args, which == 0 ? a.lds_g : a.lds_l, s);
+  return hipLaunchKernel(kernel_for(a, true), dim3(blocks), dim3(kBlock), args, a.lds_l, s);
 }
-hipError_t launch_short(const KArgs& a, uint32_t blocks, hipStream_t s) { return launch_kernel(a, 2, blocks, s); }
-// one iteration is the short-electron launch, the photon launch and the
-// e-/e+ launch
-hipError_t launch_visit(const KArgs& a, bool photons, uint32_t blocks, hipStream_t s) {
-  return launch_kernel(a, photons ? 0 : 1, blocks, s);
+hipError_t launch_visit(const KArgs& a, uint32_t which, uint32_t blocks, hipStream_t s) {
+  KArgs arg = a;
+  void* args[] = {&arg, &which};
+  return hipLaunchKernel(kernel_for(a, false), dim3(blocks), dim3(kBlock), args, visit_lds(a, which), s);
 }
 hipError_t launch_inject(const KArgs& a, const InjRec* rec, uint32_t n, hipStream_t s) {
   const uint32_t want = (n + kBlock - 1) / kBlock;
@@ -1252,19 +1375,17 @@ hipError_t launch_census(const KArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_census, dim3(1), dim3(64), 0, s, a);
   return hipGetLastError();
 }
-// blocks of each visit kernel that fit on one CU (registers and LDS), for
-// the variants the context launches
-hipError_t visit_occupancy(const KArgs& a, int* per_cu_g, int* per_cu_l, int* per_cu_s) {
-  int* out[3] = {per_cu_g, per_cu_l, per_cu_s};
-  for (int w = 0; w < 3; ++w) {
-    const void* f = kernel_for(a, w);
-    const uint32_t lds = w == 0 ? a.lds_g : a.lds_l;
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(out[w], f, kBlock, lds);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+// blocks of the visit launch of `which` and of the short launch (which = 0)
+// that fit on one CU (registers and LDS), for the variants the context
+// launches
+hipError_t visit_occupancy(const KArgs& a, uint32_t which, int* per_cu) {
+  const void* f = kernel_for(a, which == 0);
+  const uint32_t lds = which == 0 ? a.lds_l : visit_lds(a, which);
+  // (the largest of the kernel's launches: the attribute is the kernel's)
+  const uint32_t most = which == 0 || a.split ? (a.lds_l > a.lds_g ? a.lds_l : a.lds_g) : a.lds_gl;
+  hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+  if (e != hipSuccess) return e;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, kBlock, lds);
 }
 #endif  // EMS_SLAB_F32_TU
 

@@ -12,13 +12,14 @@
 
 namespace ems {
 
-hipError_t launch_visit(const KArgs& a, bool photons, uint32_t blocks, hipStream_t s);
+// visit launch of the species `which` (bit 0: photons, bit 1: e-/e+)
+hipError_t launch_visit(const KArgs& a, uint32_t which, uint32_t blocks, hipStream_t s);
 hipError_t launch_inject(const KArgs& a, const InjRec* rec, uint32_t n, hipStream_t s);
 hipError_t launch_census(const KArgs& a, hipStream_t s);
 hipError_t launch_atomic_probe(double* cells, uint64_t n_cells, uint64_t n_ops, hipStream_t s);
 hipError_t launch_reset_rows(const KArgs& a, const uint32_t* rows, uint32_t n, hipStream_t s);
 hipError_t launch_gather_rows(const KArgs& a, const uint32_t* rows, uint32_t n, char* out, hipStream_t s);
-hipError_t visit_occupancy(const KArgs& a, int* per_cu_g, int* per_cu_l, int* per_cu_s);
+hipError_t visit_occupancy(const KArgs& a, uint32_t which, int* per_cu);
 hipError_t launch_short(const KArgs& a, uint32_t blocks, hipStream_t s);
 // primaries in device memory: check pass (chk: first invalid, species
 // counts) and stage pass (injection records with ids) of k of them
@@ -81,7 +82,7 @@ struct ems_ctx {
   char* ws = nullptr;
   hipStream_t stream = nullptr;
   KArgs args{};
-  uint32_t blocks_g = 0, blocks_l = 0, blocks_s = 0;
+  uint32_t blocks_v = 0, blocks_s = 0;  // visit and short launches
   std::vector<uint64_t> row_count;
   std::vector<uint32_t> keys;  // RNG event key per row (host; travels with each injected track)
   // where the batch's primaries came from since the last reset (0: none,

@@ -3,6 +3,9 @@ oracle at the edges of that rule (fewer tracks than waves, one to 64 tracks a
 wave with and without remainder, more than the waves hold at once), with few
 blocks so that small inputs reach them.  Bars: those of the random-track
 history test (energies 1e-11, deposits 5e-11 relative, positions 1e-9 mm)."""
+import dataclasses
+
+import numpy as np
 import pytest
 
 import ems_inputs as I
@@ -24,3 +27,20 @@ def test_histories_at_the_edges_of_the_wave_shares(E, oracle_mod, blocks, n):  #
     dev = compare_logs(got["log"], ref["log"], e_rtol=1e-11, pos_atol=1e-9, dep_rtol=5e-11)
     print(f"steps {dev['n']}: {dev}", flush=True)
     assert ledger_residual(got["edep"], got["ledger"], prim).max() < 1e-9
+
+
+@pytest.mark.parametrize("n_bins,timing", [(200, False), (200, True), (800, False)])
+def test_one_launch_for_both_species_or_one_each(E, oracle_mod, n_bins, timing):  # noqa: F811
+    """One launch an iteration, two with per-kernel timing, two where the
+    tables of both species exceed LDS (800 bins: 154 + 38 KB)."""
+    print(f"{n_bins} bins, timing {timing}", flush=True)
+    geo, cfg, prim = I.workload("cal_1GeV_e-_x32")
+    cfg = dataclasses.replace(cfg, n_bins=n_bins)
+    p = prim[:6]
+    ref = oracle_mod.Oracle(geo, cfg).run(p, n_events=6)
+    got = run_gpu(E, geo, cfg, p, 6, flags=E.F_FULL_LEDGER | (E.F_KERNEL_TIMING if timing else 0))
+    for f in ("n_steps", "n_created", "n_null", "n_pair", "n_annih"):
+        assert np.array_equal(got["ledger"][f], ref["ledger"][f]), f
+    assert np.allclose(got["edep"], ref["edep"], rtol=1e-9, atol=1e-9)
+    assert sum(got["stats"]["steps"]) == int(ref["ledger"]["n_steps"].sum())
+    assert (got["stats"]["kernel_ms"][0] > 0.0) == timing
