@@ -8,7 +8,7 @@
 //    e-/e+ (a concatenated index space [e- | e+]), and go on with the other
 //    species when their own is used up, so neither species' last waves leave
 //    the device idle;
-//  - the queues hold the tracks themselves (SoA, coalesced); survivors are
+//  - the queues hold the tracks themselves (64-byte records); survivors are
 //    rewritten compactly each iteration, so slots are reused by construction;
 //  - a thread keeps stepping its track (a "visit") until a step creates
 //    secondaries or ends the track, so the many boundary crossings of photons
@@ -273,17 +273,7 @@ __device__ inline void publish_counts(Ctl* ctl, const unsigned long long* cnt) {
 
 template <class R>
 __device__ inline void store_track(const Queue<R>& q, uint32_t i, const Trk<R>& t, uint32_t vb) {
-  q.x[i] = t.x;
-  q.y[i] = t.y;
-  q.z[i] = t.z;
-  q.ux[i] = t.ux;
-  q.uy[i] = t.uy;
-  q.uz[i] = t.uz;
-  q.E[i] = t.E;
-  q.id[i] = t.id;
-  q.ev[i] = t.ev;
-  q.key[i] = t.key;
-  q.ns[i] = (t.n << vb) | (uint32_t)t.slab;
+  q.store(i, t, (t.n << vb) | (uint32_t)t.slab);
 }
 
 // position of the idx-th track of a queue with `home` tracks in the bottom
@@ -599,17 +589,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
           if (spilled) nsp = 1;
           const uint32_t pos = spilled ? i - ln.n1 - ln.n2 : queue_pos(idx, home, a.cap);
           const Queue<R> src = spilled ? short_view<R>(a, 2u) : queue_view<R>(a.qbase, a.cap, ln.cur, (uint32_t)nsp);
-          nw = src.ns[pos];
-          nt.ev = src.ev[pos];
-          nt.key = src.key[pos];
-          nt.x = src.x[pos];
-          nt.y = src.y[pos];
-          nt.z = src.z[pos];
-          nt.ux = src.ux[pos];
-          nt.uy = src.uy[pos];
-          nt.uz = src.uz[pos];
-          nt.E = src.E[pos];
-          nt.id = src.id[pos];
+          nw = src.load(pos, nt);
         }
       }
       // (2) the interactions selected by the lanes' last steps, sampled
@@ -731,7 +711,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
             c.slab = o.slab;
             store_track(dq, ps, c, a.vol_bits);
           } else {
-            dq.ns[ps] = kDeadRecord;
+            dq.kill(ps);
           }
         };
         auto put_queue = [&](int q, uint32_t d, const Take& tk, uint32_t lim) {
@@ -1005,15 +985,15 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
       const Queue<R> dq = queue_view<R>(a.qbase, a.cap, ln.cur ^ 1u, (uint32_t)q);
       const uint32_t lim = ln.plan.lim[q];
       const uint32_t send = rg.hi[kNextSec + q] < lim ? rg.hi[kNextSec + q] : lim;
-      for (uint32_t x = rg.lo[kNextSec + q] + __lane_id(); x < send; x += 64) dq.ns[a.cap - 1 - x] = kDeadRecord;
+      for (uint32_t x = rg.lo[kNextSec + q] + __lane_id(); x < send; x += 64) dq.kill(a.cap - 1 - x);
       for (uint32_t x = rg.lo[kNextHome + q] + __lane_id(); x < rg.hi[kNextHome + q]; x += 64) {
-        if (x < a.cap) dq.ns[x] = kDeadRecord;
+        if (x < a.cap) dq.kill(x);
       }
     }
     if (kShort && a.cap_s) {
       const Queue<R> sq = short_view<R>(a, ln.cur ^ 1u);
       const uint32_t send = rg.hi[kNextShort] < ln.plan.lim_s ? rg.hi[kNextShort] : ln.plan.lim_s;
-      for (uint32_t x = rg.lo[kNextShort] + __lane_id(); x < send; x += 64) sq.ns[x] = kDeadRecord;
+      for (uint32_t x = rg.lo[kNextShort] + __lane_id(); x < send; x += 64) sq.kill(x);
     }
     publish_counts(ctl, cnt);
   }
@@ -1088,17 +1068,7 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   auto load = [&](uint32_t i, Trk<R>& t, uint32_t& w) {
     w = kDeadRecord;
     if (i < ns) {
-      w = src.ns[i];
-      t.x = src.x[i];
-      t.y = src.y[i];
-      t.z = src.z[i];
-      t.ux = src.ux[i];
-      t.uy = src.uy[i];
-      t.uz = src.uz[i];
-      t.E = src.E[i];
-      t.id = src.id[i];
-      t.ev = src.ev[i];
-      t.key = src.key[i];
+      w = src.load(i, t);
     }
   };
   const uint32_t stride = gridDim.x * kBlock;
@@ -1156,10 +1126,10 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   }
   sink.flush();
   for (uint32_t x = rg.lo[kNextHome + 1] + __lane_id(); x < rg.hi[kNextHome + 1]; x += 64) {
-    if (x < a.cap) dst.ns[x] = kDeadRecord;
+    if (x < a.cap) dst.kill(x);
   }
   for (uint32_t x = rg.lo[kNextSpill] + __lane_id(); x < rg.hi[kNextSpill]; x += 64) {
-    if (x < a.cap_p) spill.ns[x] = kDeadRecord;
+    if (x < a.cap_p) spill.kill(x);
   }
   count(cnt, kAddSteps + 1, steps);
   count(cnt, kAddStepsShort, steps);
