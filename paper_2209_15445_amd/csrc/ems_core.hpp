@@ -18,6 +18,8 @@
 
 #include <math.h>
 
+#include "ems_math.hpp"
+
 namespace ems {
 
 // CODATA 2018 values; kB converts p [MeV/c] = kB * B [T] * R [mm].
@@ -80,9 +82,16 @@ EMS_HD U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
 // in the callers).  These overloads pick the single- or double-precision
 // libm routine explicitly.
 EMS_HD float xlog(float v) { return logf(v); }
+// (device, FP64: the functions of ems_math.hpp; every argument is positive and
+// normal: energies, draws in (0, 1), ratios of path lengths)
+#if defined(__HIP_DEVICE_COMPILE__)
+EMS_HD double xlog(double v) { return pos_log(v); }
+EMS_HD double xexp(double v) { return ranged_exp(v); }
+#else
 EMS_HD double xlog(double v) { return log(v); }
-EMS_HD float xexp(float v) { return expf(v); }
 EMS_HD double xexp(double v) { return exp(v); }
+#endif
+EMS_HD float xexp(float v) { return expf(v); }
 EMS_HD float xsqrt(float v) { return sqrtf(v); }
 EMS_HD double xsqrt(double v) { return sqrt(v); }
 EMS_HD float xsin(float v) { return sinf(v); }
@@ -93,6 +102,13 @@ EMS_HD double xcos(double v) { return cos(v); }
 // does not merge separate sin and cos calls; about half the instructions)
 EMS_HD void xsincos(float v, float* s, float* c) { sincosf(v, s, c); }
 EMS_HD void xsincos(double v, double* s, double* c) { sincos(v, s, c); }
+// sine and cosine of a fraction u of a turn (2 pi u)
+EMS_HD void xsincos_turn(float u, float* s, float* c) { sincosf((float)kTwoPi * u, s, c); }
+#if defined(__HIP_DEVICE_COMPILE__)
+EMS_HD void xsincos_turn(double u, double* s, double* c) { sincos_turn(u, s, c); }
+#else
+EMS_HD void xsincos_turn(double u, double* s, double* c) { sincos(kTwoPi * u, s, c); }
+#endif
 EMS_HD float xfloor(float v) { return floorf(v); }
 EMS_HD double xfloor(double v) { return floor(v); }
 EMS_HD float xceil(float v) { return ceilf(v); }
@@ -119,10 +135,12 @@ EMS_HD float as_real_u<float>(double u) {
   return f < 0x1p-25f ? 0x1p-25f : (f > 1.0f - 0x1p-24f ? 1.0f - 0x1p-24f : f);
 }
 
-// 64 bits (hi:lo) -> (0,1): top 52 bits plus one half ulp, exactly representable
+// 64 bits (hi:lo) -> (0,1): top 52 bits plus one half ulp, exactly
+// representable: the 52 bits as the fraction of a number in [1, 2), minus
+// 1 - 2^-53 (exact; a conversion from integer takes twice the instructions)
 EMS_HD double to_unit(uint32_t lo, uint32_t hi) {
   const uint64_t v = ((uint64_t)hi << 32) | lo;
-  return (double)(v >> 12) * 0x1p-52 + 0x1p-53;
+  return double_of((v >> 12) | 0x3ff0000000000000ull) - (1.0 - 0x1p-53);
 }
 
 // The draws of one track step.  Block j of Philox(key, (id_lo, id_hi, step, j))
@@ -179,13 +197,13 @@ EMS_HD V3T<R> unit(V3T<R> v) {
   return V3T<R>{v.x / n, v.y / n, v.z / n};
 }
 
-// Direction with polar angle (cos t, sin t) and azimuth p about the axis u:
+// Direction with polar angle (cos t, sin t) and azimuth 2 pi turn about the axis u:
 // the frame is (e1, e2, u) with e2 = z^ x u / |z^ x u| and e1 = e2 x u;
 // u = +-z^ uses e1 = (+-1, 0, 0), e2 = (0, 1, 0).
 template <class R>
-EMS_HD V3T<R> about_axis(V3T<R> u, R cost, R sint, R phi) {
+EMS_HD V3T<R> about_axis(V3T<R> u, R cost, R sint, R turn) {
   R sp, cp;
-  xsincos(phi, &sp, &cp);
+  xsincos_turn(turn, &sp, &cp);
   const R a = sint * cp, b = sint * sp;
   const R t2 = xfma(u.x, u.x, u.y * u.y);
   if (t2 > R(0)) {

@@ -123,7 +123,7 @@ EMS_HD void compton(double E, V3T<R> u, Draws& r, Outcome<R>& o) {
   }
   const R cost = R(1) - omc;
   const R s2 = R(1) - cost * cost;
-  const V3T<R> ug = about_axis(u, cost, xsqrt(s2 > R(0) ? s2 : R(0)), R(kTwoPi) * r.u<R>());
+  const V3T<R> ug = about_axis(u, cost, xsqrt(s2 > R(0) ? s2 : R(0)), r.u<R>());
   const R ep = eps * Er;  // scattered photon energy in the arithmetic type
   o.survives = true;
   o.e_parent = (double)eps * E;
@@ -194,7 +194,7 @@ EMS_HD void delta_ray(double T, double td, V3T<R> u, Draws& r, Outcome<R>& o) {
   const R Tr = (R)T, tr = (R)td;
   const R c = xsqrt(tr * (Tr + R(2) * R(kMe)) / (Tr * (tr + R(2) * R(kMe))));
   const R s2 = R(1) - c * c;
-  const V3T<R> ud = about_axis(u, c, xsqrt(s2 > R(0) ? s2 : R(0)), R(kTwoPi) * r.u<R>());
+  const V3T<R> ud = about_axis(u, c, xsqrt(s2 > R(0) ? s2 : R(0)), r.u<R>());
   const R p = xsqrt(Tr * (Tr + R(2) * R(kMe))), pd = xsqrt(tr * (tr + R(2) * R(kMe)));
   o.survives = true;
   o.e_parent = T - td;
@@ -256,7 +256,7 @@ EMS_HD void annihilate(double T, V3T<R> u, Draws& r, Outcome<R>& o) {
   const double etot = T + 2.0 * kMe;
   R c = (eps * (g + R(1)) - R(1)) / (eps * s);
   c = c > R(1) ? R(1) : (c < R(-1) ? R(-1) : c);
-  const V3T<R> u0 = about_axis(u, c, xsqrt(R(1) - c * c), R(kTwoPi) * r.u<R>());
+  const V3T<R> u0 = about_axis(u, c, xsqrt(R(1) - c * c), r.u<R>());
   const double k0 = (double)eps * etot;
   const R k0r = (R)k0, p = (R)sqrt(T * (T + 2.0 * kMe));
   o.survives = false;
@@ -274,11 +274,11 @@ EMS_HD void annihilate(double T, V3T<R> u, Draws& r, Outcome<R>& o) {
 template <class R>
 EMS_HD void annihilate_at_rest(Draws& r, Outcome<R>& o) {
   const R c = R(2) * r.u_at<R>(1) - R(1);
-  const R phi = R(kTwoPi) * r.u_at<R>(2);
+  const R turn = r.u_at<R>(2);
   const R s2 = R(1) - c * c;
   const R sn = xsqrt(s2 > R(0) ? s2 : R(0));
   R sp, cp;
-  xsincos(phi, &sp, &cp);
+  xsincos_turn(turn, &sp, &cp);
   const V3T<R> a{sn * cp, sn * sp, c};
   o.survives = false;
   o.n = 2;

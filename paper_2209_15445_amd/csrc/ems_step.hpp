@@ -542,7 +542,7 @@ EMS_HD void msc_deflect(R th0, Draws& r, Trk<R>& t) {
   th = th > R(kPi) ? R(kPi) : th;
   R st, ct;
   xsincos(th, &st, &ct);
-  const V3T<R> d = about_axis(V3T<R>{t.ux, t.uy, t.uz}, ct, st, R(kTwoPi) * u2);
+  const V3T<R> d = about_axis(V3T<R>{t.ux, t.uy, t.uz}, ct, st, u2);
   t.ux = d.x;
   t.uy = d.y;
   t.uz = d.z;
