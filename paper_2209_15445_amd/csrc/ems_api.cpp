@@ -261,17 +261,13 @@ StepEnv<double> env_for(const ems_config* c, const ems_geometry* g, const TableS
   StepEnv<double> e{};
   e.nodes = ts.nodes;
   e.n_slabs = n_cols(g);  // deposit columns (slabs, or boxes + world)
-  e.lnemin = ts.lnemin;
-  e.dlog = ts.dlog;
-  e.inv_dlog = 1.0 / ts.dlog;
+  static_cast<StepReals<double>&>(e) = StepReals<double>{ts.lnemin, ts.dlog, 1.0 / ts.dlog, (double)(ts.nodes - 2),
+                                                         c->dr_over_range, c->final_range_mm, c->lin_loss_limit};
   e.half_xy = g->half_xy_mm;
   e.bz = c->bz_tesla;
   e.ecut = c->emin_MeV;
   e.tcut = c->electron_cut_MeV;
   e.kcut = c->gamma_cut_MeV;
-  e.alpha = c->dr_over_range;
-  e.rho = c->final_range_mm;
-  e.lin = c->lin_loss_limit;
   e.mask = c->process_mask;
   e.seed = c->seed;
   e.max_steps = c->max_steps_per_track;
@@ -656,6 +652,8 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
   a.photon_refill_below = cfg->photon_refill_below;
   a.precision = cfg->precision == EMS_MIXED ? 1u : 0u;
   a.env = env_for(cfg, geo, c->ts);
+  a.env32 = reals<float, double>(a.env);
+  a.qstride = L.cap * queue_track_bytes(cfg);
   a.geo = geo->n_boxes ? 1u : 0u;
   a.vol_bits = vol_bits(geo);
   // the smallest kernel variants that cover the configuration's optional

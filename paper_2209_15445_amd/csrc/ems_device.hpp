@@ -100,12 +100,6 @@ EMS_HD void view_at(char* b, uint64_t cap, Queue<double>& q) {
   q.tail = reinterpret_cast<TrackTail64*>(q.rec + cap);
 }
 EMS_HD void view_at(char* b, uint64_t, Queue<float>& q) { q.rec = reinterpret_cast<TrackRec32*>(b); }
-template <class R>
-EMS_HD Queue<R> queue_view(char* base, uint64_t cap, uint32_t buf, uint32_t sp) {
-  Queue<R> q;
-  view_at(base + (size_t)(buf * 3u + sp) * cap * track_bytes<R>(), cap, q);
-  return q;
-}
 
 // Loop control, written by the last block of each step launch.
 //
@@ -211,6 +205,7 @@ struct KArgs {
   uint32_t* profile;   // [profile_cap][3]
   int32_t* live_ev;    // [rows] live tracks per event (kFlagEventLive)
   uint64_t cap;        // tracks per species per buffer
+  uint64_t qstride;    // bytes of a queue buffer (cap records)
   uint32_t max_events;  // tally rows
   uint64_t log_cap;
   uint32_t profile_cap;
@@ -230,6 +225,7 @@ struct KArgs {
   uint32_t feat;              // optional parts (kF* bits) of the kernels launched
   uint32_t vol_bits;          // low bits of the packed word that hold the volume
   StepEnv<double> env;  // scalars; its pointers are set per block
+  StepReals<float> env32;  // env's StepReals in the mixed form's arithmetic type
   // Short electrons: e- secondaries below short_E (0: none) are appended to
   // a buffer of their own (two of cap_s records, current and next) and take
   // their first step in a launch of their own at the start of the next
@@ -241,11 +237,21 @@ struct KArgs {
   uint32_t waves_s;           // waves of the short launch
 };
 
+// queue of species sp in buffer buf (0/1)
+template <class R>
+EMS_HD Queue<R> queue_view(const KArgs& a, uint32_t buf, uint32_t sp) {
+  Queue<R> q;
+  // (by selection: sp may differ between lanes, the rest does not)
+  const uint64_t at = sp == 0 ? 0ull : (sp == 1 ? a.qstride : 2 * a.qstride);
+  view_at(a.qbase + (buf ? 3 * a.qstride : 0ull) + at, a.cap, q);
+  return q;
+}
 // short buffer b (0/1) and the spill buffer (b = 2), laid out as queues
 template <class R>
 EMS_HD Queue<R> short_view(const KArgs& a, uint32_t b) {
-  char* base = a.sbase + (size_t)b * a.cap_s * track_bytes<R>();
-  return queue_view<R>(base, b == 2 ? a.cap_p : a.cap_s, 0, 0);
+  Queue<R> q;
+  view_at(a.sbase + (size_t)b * a.cap_s * track_bytes<R>(), b == 2 ? a.cap_p : a.cap_s, q);
+  return q;
 }
 
 }  // namespace ems

@@ -285,50 +285,42 @@ __device__ inline uint32_t queue_pos(uint32_t idx, uint32_t home, uint64_t cap) 
 // Tallies of one applied step: FP64 atomic scoring per (event, slab), energy
 // ledger, optional per-event counts and step log.
 struct DevSink {
-  double* edep;
-  LedgerDev* ledger;
-  Ctl* ctl;
-  StepRec* log;
-  unsigned long long log_cap;
-  uint32_t n_slabs;
-  bool full, logging;
   // deposits of consecutive steps into the same (event, slab) add up in the
   // lane and reach the tally with one atomic when the cell changes or the
   // lane finishes (summation order of FP64 atomics is unordered anyway)
-  size_t acc_cell;
-  double acc_dep;
-  ExitRec* exits;
-  uint64_t exit_cap;
+  size_t acc_cell = 0;
+  double acc_dep = 0.0;
 
-  __device__ void flush() {
-    if (acc_dep != 0.0) atomicAdd(&edep[acc_cell], acc_dep);
+  __device__ void flush(const KArgs& a) {
+    if (acc_dep != 0.0) atomicAdd(&a.edep[acc_cell], acc_dep);
     acc_dep = 0.0;
   }
 
   // F: the kernel's optional parts; the per-step records (exits, full
   // ledger, step log) exist only with kFRecord
   template <int F, class R>
-  __device__ void apply(int sp, const Trk<R>& t, const StepOut<R>& o, double e_before) {
+  __device__ void apply(const KArgs& a, int sp, const Trk<R>& t, const StepOut<R>& o, double e_before) {
+    Ctl* const ctl = a.ctl;
     if (o.dep != 0.0) {
-      const size_t cell = (size_t)t.ev * n_slabs + o.slab;
+      const size_t cell = (size_t)t.ev * a.env.n_slabs + o.slab;
       if (cell != acc_cell) {
-        flush();
+        flush(a);
         acc_cell = cell;
       }
       acc_dep += o.dep;
     }
-    LedgerDev& L = ledger[t.ev];
+    LedgerDev& L = a.ledger[t.ev];
     if (o.escaped != 0.0) atomicAdd(&L.escaped[0] + sp, o.escaped);
     if (o.killed != 0.0) atomicAdd(&L.killed, o.killed);
     if (o.pair) atomicAdd(&L.n_pair, (uint32_t)o.pair);
     if (o.annih) atomicAdd(&L.n_annih, (uint32_t)o.annih);
     if constexpr ((F & kFRecord) == 0) return;
-    if (exit_cap) {
+    if (a.exit_cap) {
       // the track left the stack: its state at the exit point
       const bool out = o.escaped != 0.0;
       const unsigned long long i = active_append(&ctl->exit_n, out);
-      if (out && i < exit_cap) {
-        ExitRec& x = exits[i];
+      if (out && i < a.exit_cap) {
+        ExitRec& x = a.exits[i];
         x.event = t.ev;
         x.species = (uint32_t)sp;
         x.ekin = o.escaped;
@@ -340,17 +332,17 @@ struct DevSink {
         x.dir[2] = t.uz;
       }
     }
-    if (full) {
+    if (a.flags & kFlagFullLedger) {
       atomicAdd(&L.n_steps, 1ull);
       if (o.clen != 0.0) atomicAdd(&L.charged_len, o.clen);
       if (o.null) atomicAdd(&L.n_null, 1ull);
       if (o.nsec > 0) atomicAdd(&L.n_created[0] + o.sec[0].sp, 1ull);
       if (o.nsec > 1) atomicAdd(&L.n_created[0] + o.sec[1].sp, 1ull);
     }
-    if (logging) {
+    if (a.flags & kFlagSteplog) {
       const unsigned long long ls = atomicAdd(&ctl->log_n, 1ull);
-      if (ls < log_cap) {
-        StepRec& r = log[ls];
+      if (ls < a.log_cap) {
+        StepRec& r = a.log[ls];
         r.event = t.ev;
         r.species = (uint32_t)sp;
         r.id = t.id;
@@ -382,11 +374,19 @@ __device__ inline R* stage_tables(const void* src, uint32_t n, char*& lds) {
   lds += (n * sizeof(R) + 7) / 8 * 8;
   return dst;
 }
+// what a block holds in LDS
+template <class R>
+struct Staged {
+  const R *tg, *tl;
+  const double* zplane;
+  const MatRT* mat;
+  const uint32_t* slab_mat;
+};
 template <class R, int GEO>
-__device__ StepEnv<R> stage(const KArgs& a, char* lds, uint32_t which) {
-  StepEnv<R> env = retype<R>(a.env);
-  if (which & kPhotons) env.tg = stage_tables<R>(a.tab_g, a.n_mat * kGammaTables * a.env.nodes, lds);
-  if (which & kLeptons) env.tl = stage_tables<R>(a.tab_l, a.n_mat * kLeptonTables * a.env.nodes, lds);
+__device__ Staged<R> stage(const KArgs& a, char* lds, uint32_t which) {
+  Staged<R> st{nullptr, nullptr, nullptr, nullptr, nullptr};
+  if (which & kPhotons) st.tg = stage_tables<R>(a.tab_g, a.n_mat * kGammaTables * a.env.nodes, lds);
+  if (which & kLeptons) st.tl = stage_tables<R>(a.tab_l, a.n_mat * kLeptonTables * a.env.nodes, lds);
   double* zp = reinterpret_cast<double*>(lds);
   // a box geometry reads its volume materials from global memory
   const uint32_t nz = GEO == 1 ? 0u : a.env.n_slabs + 1, nsm = GEO == 1 ? 0u : a.env.n_slabs;
@@ -396,12 +396,55 @@ __device__ StepEnv<R> stage(const KArgs& a, char* lds, uint32_t which) {
   uint32_t* sm = reinterpret_cast<uint32_t*>(mr + a.n_mat);
   for (uint32_t i = threadIdx.x; i < nsm; i += kBlock) sm[i] = a.slab_mat[i];
   __syncthreads();
-  env.zplane = GEO == 1 ? nullptr : zp;
-  env.mat = mr;
-  env.elc = a.el_c;
-  env.elt = static_cast<const R*>(a.el_tab);
-  env.slab_mat = GEO == 1 ? a.slab_mat : sm;
-  return env;
+  st.zplane = zp;
+  st.mat = mr;
+  st.slab_mat = sm;
+  return st;
+}
+
+// The kernel's arguments as its first parameter holds them, read anew: a
+// wave needs some eighty scalars over one iteration of its loop, more than
+// fit the scalar registers beside its own state, and a value that is kept
+// is spilled to lanes of vector registers and fetched back one word an
+// instruction.  Reading them again from the argument segment (scalar cache)
+// where a part of the loop begins keeps them out of the other parts: spilled
+// scalars of the FP64 kernel 228 -> 150 (fetches and stores of them 1554 ->
+// 484 of 12 000 instructions), 10^4 x 10 GeV 48.9 -> 46.1 ms, 40 000 x 10 GeV
+// in the mixed form 127.6 -> 118.6 ms.
+__device__ __forceinline__ const KArgs& fresh_args() {
+  using Arg = const __attribute__((address_space(4))) KArgs;
+  Arg* p = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const KArgs*)p;
+}
+template <class R>
+__device__ __forceinline__ StepReals<R> reals_of(const KArgs& a) {
+  if constexpr (sizeof(R) == 4) return a.env32;
+  else return a.env;
+}
+template <class R, int GEO>
+__device__ __forceinline__ StepEnv<R> env_of(const KArgs& a, const Staged<R>& st) {
+  StepEnv<R> e;
+  e.tg = st.tg;
+  e.tl = st.tl;
+  e.zplane = GEO == 1 ? nullptr : st.zplane;
+  e.slab_mat = GEO == 1 ? a.slab_mat : st.slab_mat;
+  e.mat = st.mat;
+  if constexpr (GEO == 1) e.nav = a.env.nav;
+  e.elc = a.el_c;
+  e.elt = static_cast<const R*>(a.el_tab);
+  e.nodes = a.env.nodes;
+  e.n_slabs = a.env.n_slabs;
+  static_cast<StepReals<R>&>(e) = reals_of<R>(a);
+  e.half_xy = a.env.half_xy;
+  e.bz = a.env.bz;
+  e.ecut = a.env.ecut;
+  e.tcut = a.env.tcut;
+  e.kcut = a.env.kcut;
+  e.mask = a.env.mask;
+  e.seed = a.env.seed;
+  e.max_steps = a.env.max_steps;
+  return e;
 }
 
 }  // namespace
@@ -472,8 +515,8 @@ struct Launch {
 };
 
 template <bool PHOTONS, class R, int GEO, int F>
-__device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepEnv<R>& env, const Launch& ln,
-                                           const WaveShare& share, Ranges& rg) {
+__device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const Launch& ln, const WaveShare& share,
+                                           Ranges& rg) {
   constexpr int KIND = PHOTONS ? 0 : 1;
   constexpr bool kShort = (F & kFShort) != 0;
   // a step changes the direction itself (before any interaction)
@@ -482,16 +525,15 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
   constexpr int kSecA = PHOTONS ? kElectron : kGamma, kSecB = PHOTONS ? kPositron : kElectron;
   const uint32_t nmine = PHOTONS ? ln.n0 : ln.n1 + ln.n2 + ln.np;
   const uint32_t nxt = ln.cur ^ 1u;
-  const int max_visit = (int)(PHOTONS ? a.photon_steps_per_visit : a.steps_per_visit);
-  const uint32_t refill_below = PHOTONS ? a.photon_refill_below : a.refill_below;
+  const KArgs& a0 = fresh_args();
+  const int max_visit = (int)(PHOTONS ? a0.photon_steps_per_visit : a0.steps_per_visit);
+  const uint32_t refill_below = PHOTONS ? a0.photon_refill_below : a0.refill_below;
   const Plan& plan = ln.plan;
   // short-electron routing: compiled into the kFShort variants only
-  const bool shorts = kShort && a.cap_s != 0;
-  DevSink sink{a.edep, a.ledger, ctl, a.log, a.log_cap, a.env.n_slabs,
-               (a.flags & kFlagFullLedger) != 0, (a.flags & kFlagSteplog) != 0, 0, 0.0,
-               a.exits, a.exit_cap};
+  const bool shorts = kShort && a0.cap_s != 0;
+  DevSink sink;
   uint32_t* cursor = &ctl->cursor[PHOTONS ? 0 : 1];
-  const bool track_live = (F & kFRecord) && (a.flags & kFlagEventLive) != 0;
+  const bool track_live = (F & kFRecord) && (a0.flags & kFlagEventLive) != 0;
 
   bool has = false;   // lane holds a track (inside a visit or waiting to commit)
   bool fin = false;   // its visit ended; outputs wait for the batch commit
@@ -534,18 +576,19 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
   GeoPre world_pre{0.0, Face{0, 0.0, 0, -1}};
   // (charged tracks in a field search their boundary along the helix
   // within their own step limit: they take no straight-line distance)
-  const bool world_batch = PHOTONS || !((F & kFField) && env.bz != 0.0);
+  const bool world_batch = PHOTONS || !((F & kFField) && a0.env.bz != 0.0);
+  const uint32_t world = GEO == 1 ? a0.env.nav.n_boxes : 0u;
   for (;;) {
     bool world_wait = false;
     if constexpr (GEO == 1)
-      world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == env.nav.n_boxes;
+      world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == world;
     uint32_t stepping = (uint32_t)__popcll(__ballot(has && !fin && !world_wait));
     if constexpr (GEO == 1) {
       const uint32_t nw = (uint32_t)__popcll(__ballot(world_wait));
       if (nw && (nw >= world_min || stepping == 0)) {
         if (world_wait) {
           const double p[3] = {t.x, t.y, t.z}, u[3] = {(double)t.ux, (double)t.uy, (double)t.uz};
-          world_pre.s = box_distance(env.nav, t.slab, p, u, world_pre.fc);
+          world_pre.s = box_distance(fresh_args().env.nav, t.slab, p, u, world_pre.fc);
           world_ready = true;
           world_wait = false;
         }
@@ -554,6 +597,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
     }
     // batch point: few lanes still stepping
     if (stepping == 0 || (drained ? stepping <= drain_below && __ballot(fin) != 0 : stepping <= refill_below)) {
+      const KArgs& a = fresh_args();
       // (0) e-/e+: while the queue still has tracks, interactions are
       // sampled only once at least interact_min lanes wait for one (each
       // sampler costs the wave one pass however few lanes use it); until
@@ -588,7 +632,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
           const bool spilled = !PHOTONS && (F & kFShort) && i >= ln.n1 + ln.n2;  // an e- from the spill buffer
           if (spilled) nsp = 1;
           const uint32_t pos = spilled ? i - ln.n1 - ln.n2 : queue_pos(idx, home, a.cap);
-          const Queue<R> src = spilled ? short_view<R>(a, 2u) : queue_view<R>(a.qbase, a.cap, ln.cur, (uint32_t)nsp);
+          const Queue<R> src = spilled ? short_view<R>(a, 2u) : queue_view<R>(a, ln.cur, (uint32_t)nsp);
           nw = src.load(pos, nt);
         }
       }
@@ -599,7 +643,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
         uy0 = t.uy;
         uz0 = t.uz;
       }
-      if (done && o.pending) interact<KIND, F>(env, t, o);
+      if (done && o.pending) interact<KIND, F>(env_of<R, GEO>(a, st), t, o);
       // (3) the prefetched records have arrived; waiting here, before any
       // store of this batch is issued, keeps later uses of their fields
       // from waiting on those stores (vector memory completes in order)
@@ -677,7 +721,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
           if (late) hs = sp == 2 ? lp.slot(0) : lh.slot(0);
         }
         if (commit || (done && held && o.nsec == 0)) {
-          sink.apply<F>(sp, t, o, e0);
+          sink.apply<F>(a, sp, t, o, e0);
           if (sp == 2) ++steps_p;
           else ++steps_e;
           made_a += da;
@@ -716,7 +760,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
         };
         auto put_queue = [&](int q, uint32_t d, const Take& tk, uint32_t lim) {
           if (!d) return;
-          const Queue<R> dq = queue_view<R>(a.qbase, a.cap, nxt, (uint32_t)q);
+          const Queue<R> dq = queue_view<R>(a, nxt, (uint32_t)q);
           const bool first = in0 && o.sec[0].sp == q;
           const uint32_t sl = tk.slot(0);
           if (sl < lim) put(dq, first ? o.sec[0] : o.sec[1], (uint32_t)(a.cap - 1 - sl));
@@ -737,7 +781,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
           }
         }
         if (keep) {
-          const Queue<R> dq = queue_view<R>(a.qbase, a.cap, nxt, (uint32_t)sp);
+          const Queue<R> dq = queue_view<R>(a, nxt, (uint32_t)sp);
           if (hs >= a.cap) {
             atomicOr(&ctl->error, kErrOverflow);
           } else {
@@ -766,7 +810,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
           o.pending = false;
         }
         // a continuing photon has a new energy and direction
-        if (PHOTONS && cont) photon_begin(env, t, vs.pc);
+        if (PHOTONS && cont) photon_begin(env_of<R, GEO>(a, st), t, vs.pc);
       }
       // (5) the freed lanes take their prefetched tracks
       if (take) {
@@ -784,7 +828,7 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
         t.slab = nt.slab;
         sp = nsp;
         has = true;
-        visit_begin<KIND>(env, sp, t, vs);
+        visit_begin<KIND>(env_of<R, GEO>(a, st), sp, t, vs);
         world_ready = false;
         if (sp == 2) ++visits_p;
         else ++visits_e;
@@ -795,11 +839,12 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
       }
       // tracks just taken that start in the world wait for a world pass
       if constexpr (GEO == 1)
-        world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == env.nav.n_boxes;
+        world_wait = world_batch && has && !fin && !world_ready && (uint32_t)t.slab == world;
     }
 
     // one step of every lane inside a visit
     if (has && !fin && !world_wait) {
+      const KArgs& a = fresh_args();
       x0 = t.x;
       y0 = t.y;
       z0 = t.z;
@@ -809,18 +854,18 @@ __device__ __forceinline__ void visit_loop(const KArgs& a, Ctl* ctl, const StepE
         uy0 = t.uy;
         uz0 = t.uz;
       }
-      fin = visit_step<KIND, R, GEO, F>(env, sp, vs, t, o, max_visit, world_ready ? &world_pre : nullptr);
+      fin = visit_step<KIND, R, GEO, F>(env_of<R, GEO>(a, st), sp, vs, t, o, max_visit, world_ready ? &world_pre : nullptr);
       world_ready = false;
       held = o.pending;
       if (!held) {
-        sink.apply<F>(sp, t, o, e0);
+        sink.apply<F>(a, sp, t, o, e0);
         if (sp == 2) ++steps_p;
         else ++steps_e;
       }
     }
   }
 
-  sink.flush();
+  sink.flush(fresh_args());
   constexpr int kOwn = PHOTONS ? 0 : 1;
   count(ln.cnt, kAddSteps + kOwn, steps_e);
   count(ln.cnt, kAddVisits + kOwn, visits_e);
@@ -964,7 +1009,7 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
   }
   if (work && ctl->error == 0) {
     clear_counts(cnt);
-    const StepEnv<R> env = stage<R, GEO>(a, reinterpret_cast<char*>(lds_words), which);
+    const Staged<R> st = stage<R, GEO>(a, reinterpret_cast<char*>(lds_words), which);
     Ranges rg{};
     const bool own_g = w < wg;
 #pragma unroll 1
@@ -973,16 +1018,16 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
       if (turn == 1 && (photons ? ng == 0u || sg.lanes < 64u : nl == 0u || sl.lanes < 64u)) break;
       if (photons) {
         const WaveShare s = turn == 0 ? sg : WaveShare{64u, sg.pool, sg.pool};
-        visit_loop<true, R, GEO, F>(a, ctl, env, ln, s, rg);
+        visit_loop<true, R, GEO, F>(ctl, st, ln, s, rg);
       } else {
         const WaveShare s = turn == 0 ? sl : WaveShare{64u, sl.pool, sl.pool};
-        visit_loop<false, R, GEO, F>(a, ctl, env, ln, s, rg);
+        visit_loop<false, R, GEO, F>(ctl, st, ln, s, rg);
       }
     }
     // unused ends of the wave's append ranges hold no track
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const Queue<R> dq = queue_view<R>(a.qbase, a.cap, ln.cur ^ 1u, (uint32_t)q);
+      const Queue<R> dq = queue_view<R>(a, ln.cur ^ 1u, (uint32_t)q);
       const uint32_t lim = ln.plan.lim[q];
       const uint32_t send = rg.hi[kNextSec + q] < lim ? rg.hi[kNextSec + q] : lim;
       for (uint32_t x = rg.lo[kNextSec + q] + __lane_id(); x < send; x += 64) dq.kill(a.cap - 1 - x);
@@ -1047,15 +1092,14 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   const uint32_t n0 = ctl->n_home[0] + ctl->n_sec[0], n1 = ctl->n_home[1] + ctl->n_sec[1];
   const uint32_t n2 = ctl->n_home[2] + ctl->n_sec[2];
   clear_counts(cnt);
-  const StepEnv<R> env = stage<R, GEO>(a, lds, kLeptons);
+  const Staged<R> st = stage<R, GEO>(a, lds, kLeptons);
+  const StepEnv<R> env = env_of<R, GEO>(a, st);
   const Plan plan = append_plan<true>(a, n0, n1, n2, ns);
-  DevSink sink{a.edep, a.ledger, ctl, a.log, a.log_cap, a.env.n_slabs,
-               (a.flags & kFlagFullLedger) != 0, (a.flags & kFlagSteplog) != 0, 0, 0.0,
-               a.exits, a.exit_cap};
+  DevSink sink;
   const bool track_live = (F & kFRecord) && (a.flags & kFlagEventLive) != 0;
   const Queue<R> src = short_view<R>(a, cur);
   const Queue<R> spill = short_view<R>(a, 2u);
-  const Queue<R> dst = queue_view<R>(a.qbase, a.cap, cur ^ 1u, (uint32_t)kElectron);
+  const Queue<R> dst = queue_view<R>(a, cur ^ 1u, (uint32_t)kElectron);
   // wave-private append ranges: next e- home, spill buffer
   Ranges rg{};
   // spill appends: all waves' unused chunk ends fit in the spill buffer's
@@ -1098,7 +1142,7 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
         to_spill = true;
       } else {
         watchdog(env, t, o);
-        sink.apply<F>(kElectron, t, o, first.E);
+        sink.apply<F>(a, kElectron, t, o, first.E);
         ++steps;
         alive = t.slab >= 0;
         if (track_live && !alive) atomicAdd(&a.live_ev[t.ev], -1);
@@ -1124,7 +1168,7 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
     t = tn;
     w = wn;
   }
-  sink.flush();
+  sink.flush(a);
   for (uint32_t x = rg.lo[kNextHome + 1] + __lane_id(); x < rg.hi[kNextHome + 1]; x += 64) {
     if (x < a.cap) dst.kill(x);
   }
@@ -1197,7 +1241,7 @@ __global__ __launch_bounds__(kBlock) void k_inject(KArgs a, const InjRec* rec, u
       t.key = r.key;
       t.n = 0;
       t.slab = r.slab;
-      store_track(queue_view<R>(a.qbase, a.cap, cur, (uint32_t)qs), slot, t, a.vol_bits);
+      store_track(queue_view<R>(a, cur, (uint32_t)qs), slot, t, a.vol_bits);
       if (a.flags & kFlagEventLive) atomicAdd(&a.live_ev[r.ev], 1);
     }
   }

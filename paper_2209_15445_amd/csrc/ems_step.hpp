@@ -35,8 +35,16 @@ enum : int { kFField = 1, kFMsc = 2, kFFluct = 4, kFCompound = 8, kFRecord = 16,
 // [mat][12][nodes] (tables 3..14).
 constexpr int kGammaTables = 3, kLeptonTables = kNumDevTables - kGammaTables;
 
+// the environment's scalars that the step uses in the arithmetic type: the
+// energy grid (first node, spacing, last bin) and the step function
 template <class R>
-struct StepEnv {
+struct StepReals {
+  R lnemin, dlog, inv_dlog, top;
+  R alpha, rho, lin;
+};
+
+template <class R>
+struct StepEnv : StepReals<R> {
   const R* tg;               // photon table block
   const R* tl;               // lepton table block
   const double* zplane;      // n_slabs + 1
@@ -46,10 +54,8 @@ struct StepEnv {
   const double* elc;         // element screening constants [mat][4][2]
   const R* elt;              // partial pair / brems totals [mat][4][2][nodes]
   uint32_t nodes, n_slabs;
-  R lnemin, dlog, inv_dlog;
   double half_xy, bz;
   double ecut, tcut, kcut;
-  double alpha, rho, lin;
   uint32_t mask, seed, max_steps;
 
   EMS_HD const R* T(uint32_t m, int t) const {
@@ -58,6 +64,10 @@ struct StepEnv {
   }
 };
 
+template <class R, class S>
+EMS_HD StepReals<R> reals(const StepReals<S>& a) {
+  return StepReals<R>{(R)a.lnemin, (R)a.dlog, (R)a.inv_dlog, (R)a.top, (R)a.alpha, (R)a.rho, (R)a.lin};
+}
 // the scalars of an environment in another arithmetic type (table pointers
 // are left null)
 template <class R, class S>
@@ -73,17 +83,12 @@ EMS_HD StepEnv<R> retype(const StepEnv<S>& a) {
   e.elt = nullptr;
   e.nodes = a.nodes;
   e.n_slabs = a.n_slabs;
-  e.lnemin = (R)a.lnemin;
-  e.dlog = (R)a.dlog;
-  e.inv_dlog = (R)a.inv_dlog;
+  static_cast<StepReals<R>&>(e) = reals<R, S>(a);
   e.half_xy = a.half_xy;
   e.bz = a.bz;
   e.ecut = a.ecut;
   e.tcut = a.tcut;
   e.kcut = a.kcut;
-  e.alpha = a.alpha;
-  e.rho = a.rho;
-  e.lin = a.lin;
   e.mask = a.mask;
   e.seed = a.seed;
   e.max_steps = a.max_steps;
@@ -133,7 +138,7 @@ template <class R>
 EMS_HD Bin<R> bin_of(const StepEnv<R>& e, R lnE) {
   const R x = (lnE - e.lnemin) * e.inv_dlog;
   R f = xfloor(x);
-  const R top = (R)(e.nodes - 2);
+  const R top = e.top;
   f = f < R(0) ? R(0) : (f > top ? top : f);
   int j = (int)f;  // clamped again as an integer: a NaN never indexes outside
   j = j < 0 ? 0 : (j > (int)e.nodes - 2 ? (int)e.nodes - 2 : j);
@@ -231,7 +236,7 @@ EMS_HD double cont_loss(const StepEnv<R>& e, const R* Rt, int jT, double T, R S,
   R x = R(0);
   if (s >= (double)Rv) {
     L = T;
-  } else if (s < (double)(R(e.lin) * Rv)) {
+  } else if (s < (double)(e.lin * Rv)) {
     L = (double)((R)s * S);
   } else {
     x = inverse_range_ln(e, Rt, Rv - (R)s, jT + 1);
@@ -612,7 +617,7 @@ EMS_HD void lepton_step(const StepEnv<R>& e, bool positron, Trk<R>& t, StepOut<R
   if (cont) {
     S = lerp(e.T(m, positron ? tSep : tSem), b);
     Rv = lerp(Rt, b);
-    const R al = (R)e.alpha, rh = (R)e.rho;
+    const R al = e.alpha, rh = e.rho;
     scont = Rv <= rh ? Rv : al * Rv + rh * (R(1) - al) * (R(2) - rh / Rv);
   }
   const bool field = (F & kFField) && e.bz != 0.0;
@@ -679,7 +684,7 @@ EMS_HD void lepton_step(const StepEnv<R>& e, bool positron, Trk<R>& t, StepOut<R
     loss_max = sizeof(R) == 8 ? cont_loss(e, Rt, b.j, T, S, Rv, smax, &ln_lo, &have_ln)
                               : cont_loss(e, Rt, b.j, T, S, Rv, smax);
     elo = T - loss_max;
-    const R lin = (R)e.lin * Rv;
+    const R lin = e.lin * Rv;
     if (smax >= (double)lin) {
       const double e2 = T - (double)(lin * S);
       if (e2 < elo) {
