@@ -58,15 +58,23 @@ struct U4 {
   uint32_t x, y, z, w;
 };
 
+// a ^ b ^ c in one instruction (the compiler issues two)
+EMS_HD uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
+}
 EMS_HD U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int round = 0; round < 10; ++round) {
     const uint64_t a = (uint64_t)0xD2511F53u * c.x;
     const uint64_t b = (uint64_t)0xCD9E8D57u * c.z;
     U4 n;
-    n.x = (uint32_t)(b >> 32) ^ c.y ^ k0;
+    n.x = xor3((uint32_t)(b >> 32), c.y, k0);
     n.y = (uint32_t)b;
-    n.z = (uint32_t)(a >> 32) ^ c.w ^ k1;
+    n.z = xor3((uint32_t)(a >> 32), c.w, k1);
     n.w = (uint32_t)a;
     c = n;
     k0 += 0x9E3779B9u;
@@ -93,7 +101,11 @@ EMS_HD double xexp(double v) { return exp(v); }
 #endif
 EMS_HD float xexp(float v) { return expf(v); }
 EMS_HD float xsqrt(float v) { return sqrtf(v); }
+#if defined(__HIP_DEVICE_COMPILE__)
+EMS_HD double xsqrt(double v) { return plain_sqrt(v); }
+#else
 EMS_HD double xsqrt(double v) { return sqrt(v); }
+#endif
 EMS_HD float xsin(float v) { return sinf(v); }
 EMS_HD double xsin(double v) { return sin(v); }
 EMS_HD float xcos(float v) { return cosf(v); }
@@ -112,6 +124,10 @@ EMS_HD void xsincos_turn(double u, double* s, double* c) { sincos(kTwoPi * u, s,
 EMS_HD float xfloor(float v) { return floorf(v); }
 EMS_HD double xfloor(double v) { return floor(v); }
 EMS_HD float xceil(float v) { return ceilf(v); }
+EMS_HD float xmin(float a, float b) { return fminf(a, b); }
+EMS_HD double xmin(double a, double b) { return fmin(a, b); }
+EMS_HD float xmax(float a, float b) { return fmaxf(a, b); }
+EMS_HD double xmax(double a, double b) { return fmax(a, b); }
 EMS_HD float xpow(float a, float b) { return powf(a, b); }
 EMS_HD double xpow(double a, double b) { return pow(a, b); }
 EMS_HD double xceil(double v) { return ceil(v); }
@@ -193,8 +209,8 @@ using V3 = V3T<double>;
 
 template <class R>
 EMS_HD V3T<R> unit(V3T<R> v) {
-  const R n = xsqrt(v.x * v.x + v.y * v.y + v.z * v.z);
-  return V3T<R>{v.x / n, v.y / n, v.z / n};
+  const Recip<R> n(xsqrt(v.x * v.x + v.y * v.y + v.z * v.z));
+  return V3T<R>{n.of(v.x), n.of(v.y), n.of(v.z)};
 }
 
 // Direction with polar angle (cos t, sin t) and azimuth 2 pi turn about the axis u:
@@ -207,10 +223,10 @@ EMS_HD V3T<R> about_axis(V3T<R> u, R cost, R sint, R turn) {
   const R a = sint * cp, b = sint * sp;
   const R t2 = xfma(u.x, u.x, u.y * u.y);
   if (t2 > R(0)) {
-    const R t = xsqrt(t2);
-    return V3T<R>{xfma(u.x, cost, xfma(u.x * u.z, a, -(u.y * b)) / t),
-                  xfma(u.y, cost, xfma(u.y * u.z, a, u.x * b) / t),
-                  xfma(u.z, cost, -(t * a))};
+    const Recip<R> t(xsqrt(t2));
+    return V3T<R>{xfma(u.x, cost, t.of(xfma(u.x * u.z, a, -(u.y * b)))),
+                  xfma(u.y, cost, t.of(xfma(u.y * u.z, a, u.x * b))),
+                  xfma(u.z, cost, -(t.d * a))};
   }
   if (u.z > R(0)) return V3T<R>{a, b, cost};
   return V3T<R>{-a, b, -cost};

@@ -64,12 +64,12 @@ EMS_HD R screen_g(const MatRT& m, R phi) {
 template <class R>
 EMS_HD R pair_brace(const MatRT& m, R E, R eps) {
   const R w = eps * (R(1) - eps);
-  const R d = R(m.c136) * (R(kMe) / E) / w;
+  const R d = quot(R(m.c136) * quot(R(kMe), E), w);
   return (R(1) - R(2) * w) * screen_g(m, screen_phi1(d)) + (R(2) / R(3)) * w * screen_g(m, screen_phi2(d));
 }
 template <class R>
 EMS_HD R pair_bound(const MatRT& m, R E) {
-  const R dmin = R(4) * R(m.c136) * (R(kMe) / E);
+  const R dmin = R(4) * R(m.c136) * quot(R(kMe), E);
   return screen_g(m, screen_phi1_env(dmin)) + screen_g(m, screen_phi2_env(dmin)) / R(6);
 }
 
@@ -78,16 +78,16 @@ EMS_HD R pair_bound(const MatRT& m, R E) {
 template <class R>
 EMS_HD R brem_brace(const MatRT& m, R T, R k) {
   const R et = T + R(kMe);
-  const R y = k / et, w = R(1) - y;
-  const R d = R(m.c136) * R(kMe) * y / (et * w);
+  const R y = quot(k, et), w = R(1) - y;
+  const R d = quot(R(m.c136) * R(kMe) * y, et * w);
   const R v = (R(1) + w * w) * screen_g(m, screen_phi1(d)) - (R(2) / R(3)) * w * screen_g(m, screen_phi2(d));
   return v > R(0) ? v : R(0);
 }
 template <class R>
 EMS_HD R brem_bound(const MatRT& m, R T, R kc) {
   const R et = T + R(kMe);
-  const R y = kc / et;
-  const R d = R(m.c136) * R(kMe) * y / (et * (R(1) - y));
+  const R y = quot(kc, et);
+  const R d = quot(R(m.c136) * R(kMe) * y, et * (R(1) - y));
   return R(2) * screen_g(m, screen_phi1_env(d));
 }
 
@@ -110,16 +110,16 @@ struct Outcome {
 template <class R>
 EMS_HD void compton(double E, V3T<R> u, Draws& r, Outcome<R>& o) {
   const R Er = (R)E;
-  const R kap = Er / R(kMe);
-  const R e0 = R(1) / (R(1) + R(2) * kap);
+  const R kap = quot(Er, R(kMe));
+  const R e0 = quot(R(1), R(1) + R(2) * kap);
   const R a1 = -xlog(e0), a2 = R(0.5) * (R(1) - e0 * e0);
   R eps = R(1), omc = R(0);
   for (int trial = 1;; ++trial) {
     const R ra = r.u<R>(), rb = r.u<R>(), rc = r.u<R>();
     eps = (ra * (a1 + a2) < a1) ? xexp(-a1 * rb) : xsqrt(e0 * e0 + (R(1) - e0 * e0) * rb);
-    omc = (R(1) - eps) / (kap * eps);
+    omc = quot(R(1) - eps, kap * eps);
     const R s2 = omc * (R(2) - omc);
-    if (rc <= R(1) - eps * s2 / (R(1) + eps * eps) || trial >= kMaxTrials) break;
+    if (rc <= R(1) - quot(eps * s2, R(1) + eps * eps) || trial >= kMaxTrials) break;
   }
   const R cost = R(1) - omc;
   const R s2 = R(1) - cost * cost;
@@ -149,7 +149,7 @@ EMS_HD void photo(double E, V3T<R> u, Outcome<R>& o) {
 template <class R>
 EMS_HD void pair(const MatRT& m, double E, V3T<R> u, Draws& r, Outcome<R>& o) {
   const R Er = (R)E;
-  const R e0 = R(kMe) / Er, fmax = pair_bound(m, Er);
+  const R e0 = quot(R(kMe), Er), fmax = pair_bound(m, Er);
   R eps = R(0.5);
   for (int trial = 1;; ++trial) {
     const R ra = r.u<R>(), rb = r.u<R>();
@@ -172,7 +172,7 @@ template <class R>
 EMS_HD void brem(const MatRT& m, double T, double kc, V3T<R> u, Draws& r, Outcome<R>& o) {
   const R Tr = (R)T, kr = (R)kc;
   const R bound = brem_bound(m, Tr, kr);
-  const R lr = xlog(Tr / kr);
+  const R lr = xlog(quot(Tr, kr));
   R k = kr;
   for (int trial = 1;; ++trial) {
     const R ra = r.u<R>(), rb = r.u<R>();
@@ -192,7 +192,7 @@ EMS_HD void brem(const MatRT& m, double T, double kc, V3T<R> u, Draws& r, Outcom
 template <class R>
 EMS_HD void delta_ray(double T, double td, V3T<R> u, Draws& r, Outcome<R>& o) {
   const R Tr = (R)T, tr = (R)td;
-  const R c = xsqrt(tr * (Tr + R(2) * R(kMe)) / (Tr * (tr + R(2) * R(kMe))));
+  const R c = xsqrt(quot(tr * (Tr + R(2) * R(kMe)), Tr * (tr + R(2) * R(kMe))));
   const R s2 = R(1) - c * c;
   const V3T<R> ud = about_axis(u, c, xsqrt(s2 > R(0) ? s2 : R(0)), r.u<R>());
   const R p = xsqrt(Tr * (Tr + R(2) * R(kMe))), pd = xsqrt(tr * (tr + R(2) * R(kMe)));
@@ -209,13 +209,13 @@ EMS_HD void delta_ray(double T, double td, V3T<R> u, Draws& r, Outcome<R>& o) {
 template <class R>
 EMS_HD void moller(double T, double tcut, V3T<R> u, Draws& r, Outcome<R>& o) {
   const R x = (R)(tcut / T), g = (R)(T / kMe + 1.0);
-  const R gg = (g - R(1)) / g, c = gg * gg, d = (R(2) * g - R(1)) / (g * g);
+  const R gg = quot(g - R(1), g), c = gg * gg, d = quot(R(2) * g - R(1), g * g);
   const R bound = R(2) + R(0.25) * c;
   R eps = x;
   for (int trial = 1;; ++trial) {
     const R ra = r.u<R>(), rb = r.u<R>();
-    eps = x / (R(1) - ra * (R(1) - R(2) * x));
-    const R q = eps / (R(1) - eps);
+    eps = quot(x, R(1) - ra * (R(1) - R(2) * x));
+    const R q = quot(eps, R(1) - eps);
     const R f = c * eps * eps + R(1) + q * q - d * q;
     if (rb * bound <= f || trial >= kMaxTrials) break;
   }
@@ -232,7 +232,7 @@ EMS_HD void bhabha(double T, double tcut, V3T<R> u, Draws& r, Outcome<R>& o) {
   R eps = x;
   for (int trial = 1;; ++trial) {
     const R ra = r.u<R>(), rb = r.u<R>();
-    eps = x / (R(1) - ra * (R(1) - x));
+    eps = quot(x, R(1) - ra * (R(1) - x));
     const R f = ib2 + eps * (-b1 + eps * (b2 + eps * (-b3 + eps * b4)));
     if (rb * ib2 <= f || trial >= kMaxTrials) break;
   }
@@ -251,7 +251,7 @@ EMS_HD void annihilate(double T, V3T<R> u, Draws& r, Outcome<R>& o) {
   for (int trial = 1;; ++trial) {
     const R ra = r.u<R>(), rb = r.u<R>();
     eps = emin * xexp(ra * lr);
-    if (rb <= R(1) - eps + (R(2) * g * eps - R(1)) / (eps * gp2) || trial >= kMaxTrials) break;
+    if (rb <= R(1) - eps + quot(R(2) * g * eps - R(1), eps * gp2) || trial >= kMaxTrials) break;
   }
   const double etot = T + 2.0 * kMe;
   R c = (eps * (g + R(1)) - R(1)) / (eps * s);

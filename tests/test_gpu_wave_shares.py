@@ -29,10 +29,11 @@ def test_histories_at_the_edges_of_the_wave_shares(E, oracle_mod, blocks, n):  #
     assert ledger_residual(got["edep"], got["ledger"], prim).max() < 1e-9
 
 
-@pytest.mark.parametrize("n_bins,timing", [(200, False), (200, True), (800, False)])
+@pytest.mark.parametrize("n_bins,timing", [(40, False), (200, False), (200, True), (800, False)])
 def test_one_launch_for_both_species_or_one_each(E, oracle_mod, n_bins, timing):  # noqa: F811
     """One launch an iteration, two with per-kernel timing, two where the
-    tables of both species exceed LDS (800 bins: 154 + 38 KB)."""
+    tables of both species exceed LDS (800 bins: 154 + 38 KB); 40 bins: range
+    tables searched node by node."""
     print(f"{n_bins} bins, timing {timing}", flush=True)
     geo, cfg, prim = I.workload("cal_1GeV_e-_x32")
     cfg = dataclasses.replace(cfg, n_bins=n_bins)
