@@ -168,7 +168,18 @@ __device__ inline void serve(Ctl* ctl, Ranges& rg, const Ask (&a)[N]) {
 struct Plan {
   uint32_t lim[3], chunk[3];
   uint32_t lim_s, chunk_s;  // appends to the next short buffer
+  // Photons wait this iteration: less than an eighth of the e- queue is free.
+  // Photons fill an e- queue to its last slot, and one that holds nothing
+  // but e- whose next step needs a slot for a Moller electron never moves
+  // again; the last eighth is left to the e-/e+, whose secondaries mostly end
+  // in their first steps.  (While the photon queue is less than half full: a
+  // full one would hold up bremsstrahlung.)  Queues that hold the whole
+  // shower never come to this.
+  bool hold;
 };
+__device__ inline bool photons_wait(const KArgs& a, uint64_t n0, uint64_t room_e) {
+  return room_e < a.cap / 8 && n0 < a.cap / 2;
+}
 // The current short electrons (ns) may all survive their first step into
 // the next e- queue, so they count with the current e- tracks; the short
 // launch's waves also append to that queue's home region.  New short
@@ -197,6 +208,7 @@ __device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uin
     }
     p.lim_s = 0;
     p.chunk_s = 1;
+    p.hold = photons_wait(a, n0, p.lim[1]);
     return p;
   }
   const uint64_t waves = 2ull * a.waves + (a.cap_s ? a.waves_s : 0u);
@@ -215,6 +227,7 @@ __device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uin
   uint32_t cs = p.chunk[1];
   while (cs > 1 && waves * cs > a.cap_s / 4) cs >>= 1;
   p.chunk_s = cs;
+  p.hold = photons_wait(a, n0, p.lim[1]);
   p.lim_s = 0;
   if (a.cap_s) {
     const uint32_t half = p.lim[1] / 2;
@@ -662,9 +675,10 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
         // secondaries into the top regions (a step commits only if all of
         // its secondaries fit), then survivors or carried tracks
         // e- secondaries below short_E go to the next short buffer
-        const bool s0 = shorts && done && o.nsec > 0 && o.sec[0].sp == kElectron && o.sec[0].E < a.short_E;
-        const bool s1 = shorts && done && o.nsec > 1 && o.sec[1].sp == kElectron && o.sec[1].E < a.short_E;
-        const bool in0 = done && o.nsec > 0 && !s0, in1 = done && o.nsec > 1 && !s1;  // to the queues
+        const bool made = done && o.nsec > 0, hold = PHOTONS && plan.hold;
+        const bool s0 = shorts && made && !hold && o.sec[0].sp == kElectron && o.sec[0].E < a.short_E;
+        const bool s1 = shorts && made && !hold && o.nsec > 1 && o.sec[1].sp == kElectron && o.sec[1].E < a.short_E;
+        const bool in0 = made && !hold && !s0, in1 = made && !hold && o.nsec > 1 && !s1;  // to the queues
         const uint32_t da = (in0 && o.sec[0].sp == kSecA ? 1u : 0u) + (in1 && o.sec[1].sp == kSecA ? 1u : 0u);
         const uint32_t db = (in0 && o.sec[0].sp == kSecB ? 1u : 0u) + (in1 && o.sec[1].sp == kSecB ? 1u : 0u);
         const uint32_t ds = (s0 ? 1u : 0u) + (s1 ? 1u : 0u);
@@ -699,9 +713,8 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
         bool fits = !(da && (ta.slot(da - 1) >= lim_a || ta.slot(0) >= lim_a)) &&
                     !(db && (tb.slot(db - 1) >= lim_b || tb.slot(0) >= lim_b));
         if (shorts && ds && (ts.slot(ds - 1) >= plan.lim_s || ts.slot(0) >= plan.lim_s)) fits = false;
-        const bool pending = done && o.nsec > 0;
-        const bool commit = pending && fits;
-        const bool carry = pending && !fits;  // back to the state before the last step
+        const bool commit = made && fits && !hold;
+        const bool carry = made && !commit;  // back to the state before the last step
         const bool cont = done && t.slab >= 0 && !carry && will_continue;  // stays in the lane
         const bool keep = leave || carry;                                  // written to the next queue
         uint32_t hs = sp == 2 ? tp.slot(0) : th.slot(0);
@@ -998,16 +1011,19 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
   uint32_t wg = (uint32_t)((uint64_t)waves * ng / ((uint64_t)ng + nl + (ng + nl == 0u)));
   if (ng) wg = wg < 1u ? 1u : wg;
   if (nl) wg = wg < waves ? wg : waves - 1u;
-  // consecutive waves of a species go to different blocks (and so CUs)
+  // consecutive waves go to different blocks (and so CUs); the waves with a
+  // share come first, photons then e-/e+, and only their blocks take part:
+  // the others end at once, without a ticket below (an iteration without
+  // tracks, of which a chunk may hold a dozen: 10 us with 512 tickets)
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
   const WaveShare sg = wave_share(ng, w, wg ? wg : 1u);
-  const WaveShare sl = wave_share(nl, w - wg, waves > wg ? waves - wg : 1u);
-  bool work = false;
-  for (uint32_t k = 0; k < kBlock / 64; ++k) {
-    const uint32_t wk = k * gridDim.x + blockIdx.x;
-    work = work || (wk < wg ? (uint64_t)wk * sg.lanes < ng : (uint64_t)(wk - wg) * sl.lanes < nl);
-  }
-  if (work && ctl->error == 0) {
+  const uint32_t wl = waves - wg;
+  if (sg.lanes < 64u) wg = (ng + sg.lanes - 1) / sg.lanes;
+  const WaveShare sl = wave_share(nl, w - wg, wl ? wl : 1u);
+  const uint32_t used = wg + (sl.lanes < 64u ? (nl + sl.lanes - 1) / sl.lanes : wl);
+  const uint32_t workers = used < gridDim.x ? used : gridDim.x;
+  if (blockIdx.x >= workers && (workers || blockIdx.x)) return;
+  if (workers && ctl->error == 0) {
     clear_counts(cnt);
     const Staged<R> st = stage<R, GEO>(a, reinterpret_cast<char*>(lds_words), which);
     Ranges rg{};
@@ -1015,7 +1031,9 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
 #pragma unroll 1
     for (int turn = 0; turn < 2; ++turn) {
       const bool photons = own_g == (turn == 0);
-      if (turn == 1 && (photons ? ng == 0u || sg.lanes < 64u : nl == 0u || sl.lanes < 64u)) break;
+      // (a species without tracks or not in this launch; a wave helps only
+      // where the shares left tracks over)
+      if (photons ? ng == 0u || (turn == 1 && sg.lanes < 64u) : nl == 0u || (turn == 1 && sl.lanes < 64u)) continue;
       if (photons) {
         const WaveShare s = turn == 0 ? sg : WaveShare{64u, sg.pool, sg.pool};
         visit_loop<true, R, GEO, F>(ctl, st, ln, s, rg);
@@ -1050,9 +1068,9 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
   if (threadIdx.x >= 64) return;
   __builtin_amdgcn_s_waitcnt(kWaitVmem);
   uint32_t ticket = 0;
-  if (threadIdx.x == 0) ticket = atomicAdd(&ctl->blocks_done, 1u);
+  if (workers && threadIdx.x == 0) ticket = atomicAdd(&ctl->blocks_done, 1u);
   ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)ticket);
-  if (ticket == gridDim.x - 1) close_iteration<kShort>(a, ctl, ln);
+  if (!workers || ticket == workers - 1) close_iteration<kShort>(a, ctl, ln);
 }
 
 // Short electrons.  Most e- secondaries of a shower are slow (Compton and

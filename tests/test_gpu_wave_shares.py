@@ -45,3 +45,22 @@ def test_one_launch_for_both_species_or_one_each(E, oracle_mod, n_bins, timing):
     assert np.allclose(got["edep"], ref["edep"], rtol=1e-9, atol=1e-9)
     assert sum(got["stats"]["steps"]) == int(ref["ledger"]["n_steps"].sum())
     assert (got["stats"]["kernel_ms"][0] > 0.0) == timing
+
+
+@pytest.mark.parametrize("capacity", [224, 256, 1024])
+@pytest.mark.parametrize("short", [0.0, 1.0])
+def test_nearly_full_queues_keep_moving(E, capacity, short):  # noqa: F811
+    """Queues far smaller than the shower (photons wait while less than an
+    eighth of the e- queue is free): every run ends, with the results of
+    queues that hold everything."""
+    print(f"capacity {capacity}, short {short}", flush=True)
+    geo, cfg, prim = I.workload("cal_1GeV_e-_x32")
+    p = prim[:8]
+    ref = run_gpu(E, geo, cfg, p, 8, flags=E.F_FULL_LEDGER, short=short)
+    assert ref["stats"]["deferred"] == 0
+    for _ in range(4):
+        got = run_gpu(E, geo, cfg, p, 8, flags=E.F_FULL_LEDGER, capacity=capacity, short=short)
+        assert got["stats"]["deferred"] > 0
+        for f in ("n_steps", "n_created", "n_null", "n_pair", "n_annih"):
+            assert np.array_equal(got["ledger"][f], ref["ledger"][f]), f
+        assert np.allclose(got["edep"], ref["edep"], rtol=1e-12, atol=1e-12)
