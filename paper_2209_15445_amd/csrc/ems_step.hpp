@@ -28,7 +28,11 @@ constexpr double kInf = __builtin_huge_val();
 // helix in a field, multiple scattering, loss fluctuations, a compound
 // target element, and the per-step records (step log, full ledger, exits,
 // per-event live counters).
-enum : int { kFField = 1, kFMsc = 2, kFFluct = 4, kFCompound = 8, kFRecord = 16, kFShort = 32, kFAll = 63 };
+enum : int { kFField = 1, kFMsc = 2, kFFluct = 4, kFCompound = 8, kFRecord = 16, kFShort = 32, kFAll = 63,
+             // box geometries: the caller hands over the boundary distance of every
+             // straight step from the world volume (GeoPre), so the step holds no
+             // walk of the hierarchy
+             kFWorldPre = 64 };
 
 // Tables are held in two blocks so each kernel stages only its own: the
 // photon block [mat][3][nodes] (tables 0..2) and the lepton block
@@ -289,10 +293,11 @@ struct GeoPre {
   Face fc;
 };
 // Box geometry: distance to the next boundary and the face reached.
-template <class R>
+template <int F, class R>
 EMS_HD double box_dist(const StepEnv<R>& e, const Trk<R>& t, Face& fc, const double* iu = nullptr) {
   const double p[3] = {t.x, t.y, t.z}, u[3] = {(double)t.ux, (double)t.uy, (double)t.uz};
-  return box_distance(e.nav, t.slab, p, u, fc, iu);
+  if ((F & kFWorldPre) || (uint32_t)t.slab < e.nav.n_boxes) return box_exit(e.nav, (uint32_t)t.slab, p, u, fc, iu);
+  return world_distance(e.nav, p, u, fc);
 }
 // on the face reached, into the volume the track moves into, or out
 template <class R>
@@ -390,7 +395,7 @@ EMS_HD void gamma_step(const StepEnv<R>& e, Trk<R>& t, StepOut<R>& o) {
   Face fc{0, 0.0};
   double sz, sw = kInf;
   if constexpr (GEO == 1) {
-    sz = box_dist(e, t, fc);
+    sz = box_dist<0>(e, t, fc);
   } else {
     sz = dist_to_planes(e, t);
     sw = dist_to_walls(e, t);
@@ -630,7 +635,7 @@ EMS_HD void lepton_step(const StepEnv<R>& e, bool positron, Trk<R>& t, StepOut<R
         sg = pre->s;
         fc = pre->fc;
       } else {
-        sg = box_dist(e, t, fc);
+        sg = box_dist<F>(e, t, fc);
       }
       zlim = true;
     }
@@ -917,7 +922,7 @@ EMS_HD void photon_begin(const StepEnv<R>& e, const Trk<R>& t, PhotonCache<R>& p
 // One photon step with the visit cache: exactly gamma_step followed by the
 // step count and watchdog of take_step.  Returns true when the visit must
 // end after it (the photon interacted or is gone).
-template <class R, int GEO = 0>
+template <class R, int GEO = 0, int F = kFAll>
 EMS_HD bool photon_substep(const StepEnv<R>& e, const PhotonCache<R>& pc, Trk<R>& t, StepOut<R>& o,
                            const GeoPre* pre = nullptr) {
   clear_out(t, o);
@@ -942,7 +947,7 @@ EMS_HD bool photon_substep(const StepEnv<R>& e, const PhotonCache<R>& pc, Trk<R>
         fc = pre->fc;
       } else {
         const double iu[3] = {pc.iux, pc.iuy, pc.iuz};
-        sz = box_dist(e, t, fc, iu);
+        sz = box_dist<F>(e, t, fc, iu);
       }
       sw = kInf;
     } else {
@@ -1012,7 +1017,7 @@ EMS_HD bool visit_step(const StepEnv<R>& e, int sp, VisitState<R>& vs, Trk<R>& t
                        const GeoPre* pre = nullptr) {
   bool end;
   if (KIND == 0 || (KIND == 2 && sp == kGamma)) {
-    end = photon_substep<R, GEO>(e, vs.pc, t, o, pre);
+    end = photon_substep<R, GEO, F>(e, vs.pc, t, o, pre);
   } else {
     clear_out(t, o);
     lepton_step<R, GEO, F>(e, sp == kPositron, t, o, pre);

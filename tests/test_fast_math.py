@@ -1,6 +1,7 @@
 """Step code compiled for the host: the FP64 logarithm, exponential, sine and
-cosine (ems_math.hpp) against long double, and the range-table search around
-the table size from which it reads groups of nodes."""
+cosine (ems_math.hpp) against long double, the range-table search around the
+table size from which it reads groups of nodes, and the walk of the box
+hierarchy against a test of every box."""
 import os
 import subprocess
 
@@ -9,7 +10,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("name", ["fast_math_check", "range_walk_check"])
+@pytest.mark.parametrize("name", ["fast_math_check", "range_walk_check", "world_walk_check"])
 def test_host_check(tmp_path, name):
     exe = tmp_path / name
     subprocess.run(["g++", "-O2", "-ffp-contract=off", "-std=c++17", os.path.join(ROOT, "tests", name + ".cpp"), "-o",
