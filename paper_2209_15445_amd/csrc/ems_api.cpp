@@ -69,8 +69,10 @@ BoxNav host_nav(const ems_geometry* g, const BvhHost& h) {
 namespace {
 
 constexpr uint64_t kAlign = 256;
-constexpr uint32_t kInjectChunk = 1u << 18;
-constexpr uint32_t kInjectChunkNoAlloc = 1u << 14;  // static workspace: smaller staging
+// primaries staged per launch (32 short of a power of two: their bytes pay
+// for the control block's padded counters); static workspace: fewer
+constexpr uint32_t kInjectChunk = (1u << 18) - 32;
+constexpr uint32_t kInjectChunkNoAlloc = (1u << 14) - 32;
 
 uint64_t align_up(uint64_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 

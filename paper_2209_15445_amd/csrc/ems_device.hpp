@@ -110,6 +110,7 @@ EMS_HD void view_at(char* b, uint64_t, Queue<float>& q) { q.rec = reinterpret_ca
 // room for every survivor, so a step whose secondaries do not fit is simply
 // not taken: the track is carried unchanged and stepped again later (its
 // random numbers depend only on its id and step count).
+constexpr uint32_t kLine = 32;  // words of a cache line
 constexpr int kNextCounters = 8, kNextHome = 0, kNextSec = 3, kNextShort = 6, kNextSpill = 7;
 // launch tallies (Ctl::add), by species where [3]
 enum : int {
@@ -127,16 +128,11 @@ struct Ctl {
   uint32_t cur;           // index of the current buffer (0/1)
   uint32_t n_home[3];     // current queues: tracks in the home region
   uint32_t n_sec[3];      // current queues: tracks in the secondary region
-  // append counters: home (0..2) and secondary regions (3..5) of the next
-  // queues by species, next short buffer (6), and this iteration's spill
-  // buffer (7: tracks the short launch hands to the e-/e+ loop)
-  uint32_t next[kNextCounters];
   uint32_t blocks_done;   // completion ticket of the running launch
   uint32_t iteration;
   uint32_t live;          // tracks in the current queues (after the swap)
   uint32_t error;         // kErr* bits
   uint32_t peak[3];
-  uint32_t cursor[2];     // queue indices handed out (photons, e-/e+)
   unsigned long long steps[3], created[3], deferred, log_n;
   unsigned long long visits[3];  // track records loaded (one per visit)
   unsigned long long made_by[2];  // secondary records written (photon, e-/e+ launches)
@@ -152,6 +148,16 @@ struct Ctl {
   // tallies of the running iteration, folded into the totals above when it
   // ends
   unsigned long long add[kAdds];
+  // The counters every wave draws from, each alone in its cache line: they
+  // are incremented at the memory side, where the requests for one line
+  // wait for each other (in one line with each other and the fields above:
+  // 10^4 x 10 GeV 43.1 ms, 40 000 x 10 GeV in the mixed form 111.4, 500 x
+  // 2 GeV 4.49; each in its own: 40.9, 104.5 and 4.27).
+  // Append counters: home (0..2) and secondary regions (3..5) of the next
+  // queues by species, next short buffer (6), and this iteration's spill
+  // buffer (7: tracks the short launch hands to the e-/e+ loop).
+  alignas(128) uint32_t next[kNextCounters * kLine];
+  alignas(128) uint32_t cursor[2 * kLine];  // queue indices handed out (photons, e-/e+)
 };
 enum : uint32_t { kErrOverflow = 1u, kErrStall = 2u, kErrCorrupt = 4u };
 

@@ -58,31 +58,37 @@ __device__ inline uint32_t wave_reserve(uint32_t* counter, uint32_t count) {
 }
 
 // Next queue index for every lane with `want`: taken from the wave's own
-// range [lo, hi), which is refilled EMS_CURSOR_CHUNK indices at a time from
-// the launch's global cursor, so a wave pays one global atomic per chunk
-// instead of one per refill.  Every index below the cursor's final value is
-// handed out exactly once (ranges are disjoint and none is dropped).
-#ifndef EMS_CURSOR_CHUNK
-#define EMS_CURSOR_CHUNK 64
-#endif
-static_assert(EMS_CURSOR_CHUNK >= 64, "a chunk must cover a whole wave's request");
-__device__ inline uint32_t take_next(uint32_t* cursor, uint32_t pool, bool want, uint32_t& lo, uint32_t& hi) {
+// range [lo, hi), which is refilled a chunk at a time from the launch's
+// global cursor, so a wave pays one global atomic per chunk instead of one
+// per refill.  Every index below the cursor's final value is handed out
+// exactly once (ranges are disjoint and none is dropped).
+// A chunk is an eighth of an even share of what the wave knows to be left of
+// the queue's n indices, between a whole wave's request and kCursorMax, so
+// the launch still ends with small ones (40 000 x 10 GeV, mixed form: 64
+// indices always 104.5 ms, 256 always 105.9, by what is left 102.6; 10^4 x
+// 10 GeV 40.9, 43.7 and 40.9; 500 x 2 GeV 4.27, 5.75 and 4.25).
+constexpr uint32_t kCursorMin = 64, kCursorMax = 256;
+static_assert(kCursorMin >= 64, "a chunk must cover a whole wave's request");
+__device__ inline uint32_t take_next(uint32_t* cursor, uint32_t pool, bool want, uint32_t& lo, uint32_t& hi,
+                                     uint32_t n, uint32_t waves) {
   const uint64_t m = __ballot(want);
-  const uint32_t n = (uint32_t)__popcll(m);
+  const uint32_t wants = (uint32_t)__popcll(m);
   const uint32_t rank = (uint32_t)__popcll(m & __lanemask_lt());
   const uint32_t avail = hi - lo;
   uint32_t i = lo + rank;
-  if (n > avail) {
-    // the rest of the old range, then a fresh chunk (n <= 64 <= chunk size)
+  if (wants > avail) {
+    // the rest of the old range, then a fresh chunk (wants <= 64 <= chunk)
+    const uint32_t share = (n > hi ? n - hi : 0u) / 8u / waves;
+    const uint32_t chunk = share < kCursorMin ? kCursorMin : (share > kCursorMax ? kCursorMax : share);
     uint32_t base = 0;
     const int leader = __ffsll((unsigned long long)m) - 1;
-    if ((int)__lane_id() == leader) base = atomicAdd(cursor, (uint32_t)EMS_CURSOR_CHUNK);
+    if ((int)__lane_id() == leader) base = atomicAdd(cursor, chunk);
     base = __shfl(base, leader) + pool;
     if (rank >= avail) i = base + (rank - avail);
-    lo = base + (n - avail);
-    hi = base + EMS_CURSOR_CHUNK;
+    lo = base + (wants - avail);
+    hi = base + chunk;
   } else {
-    lo += n;
+    lo += wants;
   }
   return i;
 }
@@ -140,7 +146,7 @@ __device__ inline void serve(Ctl* ctl, Ranges& rg, const Ask (&a)[N]) {
   }
   uint32_t got = 0;
   if (any) {
-    if (v) got = atomicAdd(&ctl->next[lane], v);
+    if (v) got = atomicAdd(&ctl->next[lane * kLine], v);
   }
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -163,7 +169,7 @@ __device__ inline void serve(Ctl* ctl, Ranges& rg, const Ask (&a)[N]) {
 // room (so small populations append exactly); the secondary limit leaves
 // room for every survivor plus the unused chunk ends of the home region.
 #ifndef EMS_APPEND_CHUNK
-#define EMS_APPEND_CHUNK 256
+#define EMS_APPEND_CHUNK 128
 #endif
 struct Plan {
   uint32_t lim[3], chunk[3];
@@ -563,7 +569,7 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
   // short-electron routing: compiled into the kFShort variants only
   const bool shorts = kShort && a0.cap_s != 0;
   DevSink sink;
-  uint32_t* cursor = &ctl->cursor[PHOTONS ? 0 : 1];
+  uint32_t* cursor = &ctl->cursor[PHOTONS ? 0u : kLine];
   const bool track_live = (F & kFRecord) && (a0.flags & kFlagEventLive) != 0;
 
   bool has = false;   // lane holds a track (inside a visit or waiting to commit)
@@ -653,7 +659,7 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
       uint32_t nw = kDeadRecord;
       Trk<R> nt;
       if (__ballot(want) != 0) {
-        const uint32_t i = take_next(cursor, share.pool, want, chunk_lo, chunk_hi);
+        const uint32_t i = take_next(cursor, share.pool, want, chunk_lo, chunk_hi, nmine, a.waves);
         got = want && i < nmine;
         // (with fewer than 64 lanes a wave the first shares hold every track)
         drained = share.lanes < 64u || __ballot(want && i >= nmine) != 0;
@@ -928,7 +934,7 @@ __device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& l
   const uint32_t lane = __lane_id();
   uint32_t app = 0;
   unsigned long long add = 0;
-  if (lane < kNextCounters) app = atomicExch(&ctl->next[lane], 0u);
+  if (lane < kNextCounters) app = atomicExch(&ctl->next[lane * kLine], 0u);
   if (lane < kAdds) add = atomicExch(&ctl->add[lane], 0ull);
   auto next_of = [&](int c) { return (uint32_t)__builtin_amdgcn_readlane((int)app, c); };
   auto add_of = [&](int k) {
@@ -989,7 +995,7 @@ __device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& l
   }
   ctl->live = live;
   ctl->cursor[0] = 0;
-  ctl->cursor[1] = 0;
+  ctl->cursor[kLine] = 0;
   ctl->cur = ln.cur ^ 1u;
   ctl->blocks_done = 0;
 }
@@ -1025,7 +1031,7 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
   ln.n1 = ln.h1 + ctl->n_sec[1];
   ln.n2 = ln.h2 + ctl->n_sec[2];
   // the e-/e+ loop also takes the tracks the short launch spilled
-  const uint32_t np_raw = kShort ? ctl->next[kNextSpill] : 0u;
+  const uint32_t np_raw = kShort ? ctl->next[kNextSpill * (int)kLine] : 0u;
   ln.np = (uint64_t)np_raw < a.cap_p ? np_raw : (uint32_t)a.cap_p;
   // secondary slots per species that leave room for all survivors
   ln.plan = append_plan<kShort>(a, ln.n0, ln.n1, ln.n2, kShort ? ctl->n_short : 0u);
