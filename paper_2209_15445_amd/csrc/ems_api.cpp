@@ -715,10 +715,11 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
     c->graph_off = true;
   } else if (hipHostMalloc(reinterpret_cast<void**>(&c->pin_inj), (uint64_t)L.inj_chunk * sizeof(InjRec)) !=
                  hipSuccess ||
-             hipHostMalloc(reinterpret_cast<void**>(&c->pin_ctl), sizeof(Ctl)) != hipSuccess ||
+             hipHostMalloc(reinterpret_cast<void**>(&c->pin_ctl), sizeof(Ctl) + sizeof(c->chk_host)) != hipSuccess ||
              hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) {
     return bad(fail(EMS_E_DEVICE, "pinned host allocation or event creation failed"));
   }
+  if (!no_alloc) c->pin_chk = reinterpret_cast<unsigned long long*>(c->pin_ctl + 1);
   // device table layout: photon block [mat][3][nodes], then lepton block
   // [mat][10][nodes], in the arithmetic type of the chosen form
   std::vector<char> packed, elem;
@@ -858,11 +859,29 @@ ems_status ems_read_edep_device(ems_ctx* c, uint32_t first, uint32_t n, double* 
   return EMS_OK;
 }
 
+// Small reads go through the context's pinned staging, written by a kernel (a
+// copy to pageable memory is staged by the runtime: 48 rows of deposits, 38 KB,
+// 35 us by copy and 21 so; 500 rows, 400 KB, 36 and 40).  Larger ones, and all
+// of a context without pinned memory, go by copy.  (The staging's last upload
+// is earlier on the same stream.)
+static bool staged_read(const ems_ctx* c, uint64_t bytes, uint64_t limit) {
+  return !c->no_alloc && bytes <= limit && bytes <= c->L.inj_chunk * sizeof(InjRec);
+}
+constexpr uint64_t kStagedRows = 128u << 10;     // deposits
+constexpr uint64_t kStagedLedgers = 1024u << 10;  // ledgers: saves a second copy of the deposits too
+
 ems_status ems_read_edep(ems_ctx* c, uint32_t first, uint32_t n, double* out) {
   if (!c) return fail(EMS_E_INVALID, "null context");
   if (c->failed) return fail(EMS_E_STATE, "context failed earlier");
   if (!out || (uint64_t)first + n > c->cfg.max_events) return fail(EMS_E_INVALID, "rows out of range");
   const uint64_t row = c->ncols * 8ull;
+  if (n && staged_read(c, n * row, kStagedRows)) {
+    double* pin = reinterpret_cast<double*>(c->pin_inj);
+    HIPCHK(c, launch_read_rows(c->args, first, n, pin, nullptr, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    memcpy(out, pin, n * row);
+    return EMS_OK;
+  }
   HIPCHK(c, hipMemcpyAsync(out, c->ws + c->L.edep + first * row, n * row, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return EMS_OK;
@@ -872,6 +891,13 @@ ems_status ems_read_ledger(ems_ctx* c, uint32_t first, uint32_t n, ems_ledger* o
   if (!c) return fail(EMS_E_INVALID, "null context");
   if (c->failed) return fail(EMS_E_STATE, "context failed earlier");
   if (!out || (uint64_t)first + n > c->cfg.max_events) return fail(EMS_E_INVALID, "rows out of range");
+  if (n && c->ncols <= kSumCols && staged_read(c, n * sizeof(LedgerDev), kStagedLedgers)) {
+    LedgerDev* pin = reinterpret_cast<LedgerDev*>(c->pin_inj);
+    HIPCHK(c, launch_read_rows(c->args, first, n, nullptr, pin, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    memcpy(out, pin, n * sizeof(LedgerDev));
+    return EMS_OK;
+  }
   HIPCHK(c, hipMemcpyAsync(out, c->ws + c->L.ledger + first * sizeof(LedgerDev), n * sizeof(LedgerDev),
                            hipMemcpyDeviceToHost, c->stream));
   std::vector<double> ed((size_t)n * c->ncols);
@@ -890,30 +916,20 @@ ems_status ems_reset_tallies(ems_ctx* c) {
   if (!c) return fail(EMS_E_INVALID, "null context");
   if (c->failed) return fail(EMS_E_STATE, "context failed earlier");
   const Layout& L = c->L;
-  HIPCHK(c, launch_fill_zero(c->ws + L.edep, (uint64_t)c->cfg.max_events * c->ncols * 8, c->stream));
-  HIPCHK(c, launch_fill_zero(c->ws + L.ledger, (uint64_t)c->cfg.max_events * sizeof(LedgerDev), c->stream));
-  HIPCHK(c, launch_fill_zero(c->ws + L.live, (uint64_t)c->cfg.max_events * 4, c->stream));
-  if (c->args.profile_cap)
-    HIPCHK(c, launch_fill_zero(c->ws + L.profile, (uint64_t)c->args.profile_cap * 12, c->stream));
-  // keep the queues (empty after a run) but restart counters and statistics
-  HIPCHK(c, hipMemcpyAsync(c->pin_ctl, c->ws + L.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  Ctl fresh{};
-  fresh.cur = c->pin_ctl->cur;
-  for (int s = 0; s < 3; ++s) {
-    fresh.n_home[s] = c->pin_ctl->n_home[s];
-    fresh.n_sec[s] = c->pin_ctl->n_sec[s];
-    fresh.n_real[s] = c->pin_ctl->n_real[s];
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  HIPCHK(c, hipStreamIsCapturing(c->stream, &capture));
+  if (capture != hipStreamCaptureStatusNone) {  // a batch is not restarted by replays
+    c->failed = true;
+    return fail(EMS_E_DEVICE, "reset on a stream that is being captured");
   }
-  fresh.n_short = c->pin_ctl->n_short;
-  fresh.n_short_real = c->pin_ctl->n_short_real;
-  *c->pin_ctl = fresh;
-  HIPCHK(c, hipMemcpyAsync(c->ws + L.ctl, c->pin_ctl, sizeof(Ctl), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (c->source == 2) {
-    HIPCHK(c, launch_fill_zero(c->ws + L.drow, (uint64_t)c->cfg.max_events * 8, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-  }
+  // deposits, ledgers and live counters follow each other in the workspace;
+  // every region is padded to kAlign bytes
+  auto pad = [](uint64_t bytes) { return (bytes + 15) / 16 * 16; };
+  const Span zero[3] = {{c->ws + L.edep, L.live - L.edep + pad(c->cfg.max_events * 4ull)},
+                        {c->ws + L.profile, pad(c->args.profile_cap * 12ull)},
+                        {c->ws + L.drow, c->source == 2 ? pad(c->cfg.max_events * 8ull) : 0}};
+  HIPCHK(c, launch_restart(c->args, zero, c->stream));
+  c->pin_ctl->exit_n = 0;  // (the host's copy is read between chunks)
   c->source = 0;
   std::fill(c->row_count.begin(), c->row_count.end(), 0);
   c->stats = ems_run_stats{};
@@ -1169,16 +1185,27 @@ ems_status rt_enqueue_device(ems_ctx* c, const ems_primary* p, uint64_t n) {
     c->keys_dirty = false;
   }
   unsigned long long* chk = reinterpret_cast<unsigned long long*>(c->ws + L.dchk);
-  HIPCHK(c, launch_fill_zero(chk, sizeof(c->chk_host), c->stream));
-  HIPCHK(c, launch_check_primaries(c->args, p, n, chk, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->chk_host, chk, sizeof(c->chk_host), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  unsigned long long* rows = reinterpret_cast<unsigned long long*>(c->ws + L.drow);
+  const bool few = n <= kFewPrimaries;  // one launch does all (none of it if a primary is refused)
+  if (few) {
+    const Pending pend{{c->pending[0], c->pending[1], c->pending[2]}};
+    unsigned long long* res = c->pin_chk ? c->pin_chk : chk;
+    HIPCHK(c, launch_few_primaries(c->args, p, (uint32_t)n, keys, rows, pend, res, c->stream));
+    if (!c->pin_chk)
+      HIPCHK(c, hipMemcpyAsync(c->chk_host, chk, sizeof(c->chk_host), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (c->pin_chk) memcpy(c->chk_host, c->pin_chk, sizeof(c->chk_host));
+  } else {
+    HIPCHK(c, launch_fill_zero(chk, sizeof(c->chk_host), c->stream));
+    HIPCHK(c, launch_check_primaries(c->args, p, n, chk, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->chk_host, chk, sizeof(c->chk_host), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+  }
   if (c->chk_host[0]) return fail(EMS_E_INVALID, "invalid primary #" + std::to_string(n - c->chk_host[0]));
   for (int s = 0; s < 3; ++s)
     if (c->pending[s] + c->chk_host[1 + s] > c->L.cap) return fail(EMS_E_CAPACITY, "queue capacity exceeded by primaries");
   InjRec* d = reinterpret_cast<InjRec*>(c->ws + L.inj);
-  unsigned long long* rows = reinterpret_cast<unsigned long long*>(c->ws + L.drow);
-  for (uint64_t done = 0; done < n; done += L.inj_chunk) {
+  for (uint64_t done = 0; !few && done < n; done += L.inj_chunk) {
     const uint32_t k = (uint32_t)std::min<uint64_t>(L.inj_chunk, n - done);
     HIPCHK(c, launch_stage_primaries(c->args, p + done, k, keys, rows, d, c->stream));
     HIPCHK(c, launch_inject(c->args, d, k, c->stream));

@@ -26,6 +26,27 @@ hipError_t launch_short(const KArgs& a, uint32_t blocks, hipStream_t s);
 hipError_t launch_check_primaries(const KArgs& a, const void* p, uint64_t n, unsigned long long* chk, hipStream_t s);
 hipError_t launch_stage_primaries(const KArgs& a, const void* p, uint32_t k, const uint32_t* keys,
                                   unsigned long long* row_next, InjRec* out, hipStream_t s);
+// all of it in one launch for at most kFewPrimaries of them; pend: tracks
+// enqueued since the last run, by species
+constexpr uint32_t kFewPrimaries = 1024;
+struct Pending {
+  unsigned long long n[3];
+};
+hipError_t launch_few_primaries(const KArgs& a, const void* p, uint32_t n, const uint32_t* keys,
+                                unsigned long long* row_next, const Pending& pend, unsigned long long* res,
+                                hipStream_t s);
+// restart a context's batch: zero up to three spans (16-byte aligned, whole
+// 16 bytes) and the control block but for the queues' extents
+struct Span {
+  void* p;
+  uint64_t bytes;
+};
+hipError_t launch_restart(const KArgs& a, const Span (&z)[3], hipStream_t s);
+// rows [first, first + n) to (host) memory the device can write: deposits
+// (edep, or null) and ledgers with the row's sum of deposits (led, or null;
+// at most kSumCols columns)
+constexpr uint32_t kSumCols = 256;
+hipError_t launch_read_rows(const KArgs& a, uint32_t first, uint32_t n, double* edep, LedgerDev* led, hipStream_t s);
 // zero bytes at p (8-byte aligned) with a kernel on stream s
 hipError_t launch_fill_zero(void* p, uint64_t bytes, hipStream_t s);
 
@@ -91,6 +112,7 @@ struct ems_ctx {
   uint32_t source = 0;
   bool keys_dirty = true;  // keys changed since their last upload (device enqueues read them there)
   unsigned long long chk_host[4] = {0, 0, 0, 0};
+  unsigned long long* pin_chk = nullptr;  // the same, written by the device (null without pinned memory)
   uint64_t pending[3] = {0, 0, 0};
   InjRec* pin_inj = nullptr;
   Ctl* pin_ctl = nullptr;
