@@ -269,14 +269,38 @@ __device__ inline void wave_count(uint32_t* counter, uint32_t v) {
   if (__lane_id() == 0 && s) atomicAdd(counter, s);
 }
 
-// Launch tallies (Ctl::add): lanes add to the block's copy in LDS, and the
-// block adds its copy to the launch's with one instruction when it ends.
+// Launch tallies (Ctl::add): a wave sums each over its lanes, lane k keeps
+// tally k, and they are added to the block's copy in LDS with one instruction;
+// the block adds its copy to the launch's with another when it ends.  (Where
+// every lane adds to the same words the compiler sums them itself, one lane
+// after another: some 5000 instructions at the end of each of a wave's loops.
+// 300 requests 13.6 -> 12.6 ms, 32 x 1 GeV 1.80 -> 1.69, 500 x 2 GeV 4.07 ->
+// 3.98, 10^4 x 10 GeV 40.55 -> 40.37.)
 __device__ inline void clear_counts(unsigned long long* cnt) {
   if (threadIdx.x < kAdds) cnt[threadIdx.x] = 0ull;
 }
-__device__ inline void count(unsigned long long* cnt, int k, uint32_t v) {
-  if (v) atomicAdd(&cnt[k], (unsigned long long)v);
+// sum over a wave with all lanes active: within rows of 16 lanes, then the
+// rows' totals (row_shr 1, 2, 4, 8; row_bcast 15 and 31)
+__device__ inline uint32_t wave_total(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
+struct Tallies {
+  unsigned long long mine = 0;  // lane k: tally k
+  __device__ void count(int k, uint32_t v) {
+    // (halves: the sum of 64 counters may pass 32 bits)
+    const unsigned long long s = wave_total(v & 0xFFFFu) + ((unsigned long long)wave_total(v >> 16) << 16);
+    if (__lane_id() == (uint32_t)k) mine = s;
+  }
+  __device__ void add_to(unsigned long long* cnt) const {
+    if (__lane_id() < kAdds && mine) atomicAdd(&cnt[__lane_id()], mine);
+  }
+};
 // all waves of the block have counted (a barrier inside)
 __device__ inline void publish_counts(Ctl* ctl, const unsigned long long* cnt) {
   __syncthreads();
@@ -521,10 +545,10 @@ __device__ inline WaveShare wave_share(uint32_t n, uint32_t w, uint32_t waves) {
 // Minimum resident waves per SIMD the register allocation must allow, per
 // arithmetic type, geometry kind and optional parts.  FP64: 2 (at 3 the
 // kernels spill 1 KB per lane: e-/e+ 31% slower).  FP32, slab stack: 3
-// without optional parts (40 000 x 10 GeV 135 ms, at 2 157 ms); with them
-// (every such variant has the field part) and in box geometries 2 (1501
-// mixed-species events in a field 21.8 ms, at 3, with spills, 24.2 ms;
-// towers 999 x 1 GeV 13.0 ms, at 3 14.5 ms).
+// without optional parts (40 000 x 10 GeV 101.6 ms, at 4 107.5 ms; at 2 157
+// ms when at 3 it was 135); with them (every such variant has the field part)
+// and in box geometries 2 (1501 mixed-species events in a field 17.2 ms, at 3,
+// with spills, 17.8 ms; towers 999 x 1 GeV 8.8 ms, at 3 9.6 ms).
 #ifndef EMS_WAVES_F64
 #define EMS_WAVES_F64 2
 #endif
@@ -909,19 +933,21 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
 
   sink.flush(fresh_args());
   constexpr int kOwn = PHOTONS ? 0 : 1;
-  count(ln.cnt, kAddSteps + kOwn, steps_e);
-  count(ln.cnt, kAddVisits + kOwn, visits_e);
-  count(ln.cnt, kAddKept + kOwn, kept_a);
+  Tallies sums;
+  sums.count(kAddSteps + kOwn, steps_e);
+  sums.count(kAddVisits + kOwn, visits_e);
+  sums.count(kAddKept + kOwn, kept_a);
   if constexpr (!PHOTONS) {
-    count(ln.cnt, kAddSteps + 2, steps_p);
-    count(ln.cnt, kAddVisits + 2, visits_p);
-    count(ln.cnt, kAddKept + 2, kept_b);
+    sums.count(kAddSteps + 2, steps_p);
+    sums.count(kAddVisits + 2, visits_p);
+    sums.count(kAddKept + 2, kept_b);
   }
-  count(ln.cnt, kAddMade + kSecA, made_a + (kSecA == kElectron ? made_s : 0u));
-  count(ln.cnt, kAddMade + kSecB, made_b + (kSecB == kElectron ? made_s : 0u));
-  count(ln.cnt, kAddMadeBy + kOwn, made_a + made_b + made_s);
-  count(ln.cnt, kAddCarried, carried_n);
-  if constexpr (kShort) count(ln.cnt, kAddMadeShort, made_s);
+  sums.count(kAddMade + kSecA, made_a + (kSecA == kElectron ? made_s : 0u));
+  sums.count(kAddMade + kSecB, made_b + (kSecB == kElectron ? made_s : 0u));
+  sums.count(kAddMadeBy + kOwn, made_a + made_b + made_s);
+  sums.count(kAddCarried, carried_n);
+  if constexpr (kShort) sums.count(kAddMadeShort, made_s);
+  sums.add_to(ln.cnt);
 }
 
 // The last block of an iteration to end folds the tallies into the totals
@@ -1222,10 +1248,12 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   for (uint32_t x = rg.lo[kNextSpill] + __lane_id(); x < rg.hi[kNextSpill]; x += 64) {
     if (x < a.cap_p) spill.kill(x);
   }
-  count(cnt, kAddSteps + 1, steps);
-  count(cnt, kAddStepsShort, steps);
-  count(cnt, kAddVisits + 1, loads);
-  count(cnt, kAddKept + 1, kept);
+  Tallies sums;
+  sums.count(kAddSteps + 1, steps);
+  sums.count(kAddStepsShort, steps);
+  sums.count(kAddVisits + 1, loads);
+  sums.count(kAddKept + 1, kept);
+  sums.add_to(cnt);
   publish_counts(ctl, cnt);
 }
 
