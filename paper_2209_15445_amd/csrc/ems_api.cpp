@@ -667,9 +667,13 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
                           (cfg->process_mask & EMS_P_MSC ? kFMsc : 0) | (cfg->process_mask & EMS_P_FLUCT ? kFFluct : 0) |
                           (compound ? kFCompound : 0) | (record ? kFRecord : 0);
   constexpr uint32_t kAllParts = kFAll & ~kFShort;
-  a.feat = need_l == 0 ? 0u
-           : (geo->n_boxes == 0 && (need_l & ~(uint32_t)(kFField | kFRecord)) == 0) ? (uint32_t)(kFField | kFRecord)
-                                                                                    : kAllParts;
+  const auto within = [need_l](int parts) { return (need_l & ~(uint32_t)parts) == 0; };
+  if (need_l == 0) a.feat = 0;
+  else if (geo->n_boxes) a.feat = kAllParts;
+  else if (within(kFField | kFRecord)) a.feat = kFField | kFRecord;
+  else if (within(kFAlong) && !L.cap_s) a.feat = kFAlong;
+  else if (within(kFFieldCompound) && !L.cap_s) a.feat = kFFieldCompound;
+  else a.feat = kAllParts;
   // the short-electron routing is compiled into variants of its own
   if (L.cap_s) a.feat |= kFShort;
   if (cfg->flags & EMS_F_FULL_KERNELS) a.feat = kFAll;

@@ -102,7 +102,7 @@ __device__ inline uint32_t take_next(uint32_t* cursor, uint32_t pool, bool want,
 struct Ranges {
   uint32_t lo[kNextCounters], hi[kNextCounters];  // uniform
 };
-// A wave's request to one counter: cnt (0..3) slots per lane; the lane's
+// A wave's request to one counter: cnt (0..MAX) slots per lane; the lane's
 // k-th slot is slot(k).
 struct Take {
   uint32_t prefix, total, lo, avail, base;
@@ -111,13 +111,18 @@ struct Take {
     return x < avail ? lo + x : base + (x - avail);
   }
 };
+template <int MAX = 1>
 __device__ inline Take ask(const Ranges& rg, int c, uint32_t cnt) {
   const uint64_t b0 = __ballot(cnt & 1u);
-  const uint64_t b1 = __ballot((cnt >> 1) & 1u);
   const uint64_t lt = __lanemask_lt();
   Take t;
-  t.total = (uint32_t)(__popcll(b0) + 2 * __popcll(b1));
-  t.prefix = (uint32_t)(__popcll(b0 & lt) + 2 * __popcll(b1 & lt));
+  t.total = (uint32_t)__popcll(b0);
+  t.prefix = (uint32_t)__popcll(b0 & lt);
+  if constexpr (MAX > 1) {
+    const uint64_t b1 = __ballot((cnt >> 1) & 1u);
+    t.total += 2 * (uint32_t)__popcll(b1);
+    t.prefix += 2 * (uint32_t)__popcll(b1 & lt);
+  }
   t.lo = rg.lo[c];
   t.avail = rg.hi[c] - rg.lo[c];
   t.base = 0;
@@ -546,7 +551,7 @@ __device__ inline WaveShare wave_share(uint32_t n, uint32_t w, uint32_t waves) {
 // arithmetic type, geometry kind and optional parts.  FP64: 2 (at 3 the
 // kernels spill 1 KB per lane: e-/e+ 31% slower).  FP32, slab stack: 3
 // without optional parts (40 000 x 10 GeV 101.6 ms, at 4 107.5 ms; at 2 157
-// ms when at 3 it was 135); with them (every such variant has the field part)
+// ms when at 3 it was 135); with them
 // and in box geometries 2 (1501 mixed-species events in a field 17.2 ms, at 3,
 // with spills, 17.8 ms; towers 999 x 1 GeV 8.8 ms, at 3 9.6 ms).
 #ifndef EMS_WAVES_F64
@@ -565,7 +570,7 @@ template <class R, int GEO, int F>
 constexpr int visit_waves() {
   if (sizeof(R) == 8) return EMS_WAVES_F64;
   if (GEO == 1) return EMS_WAVES_BOX_F32;
-  return (F & kFField) != 0 ? EMS_WAVES_F32_FIELD : EMS_WAVES_F32;
+  return (F & ~kFShort) != 0 ? EMS_WAVES_F32_FIELD : EMS_WAVES_F32;
 }
 // What the waves of a launch share: the current queues' sizes, the append
 // plan, and where the launch's tallies go.
@@ -584,6 +589,12 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
   constexpr bool kTurns = !PHOTONS && (F & (kFField | kFMsc)) != 0;
   // secondaries: photons make e- and e+, e-/e+ make photons and e-
   constexpr int kSecA = PHOTONS ? kElectron : kGamma, kSecB = PHOTONS ? kPositron : kElectron;
+  // secondaries of one step: of a photon an e- and an e+ at most, of an e-/e+
+  // two photons (annihilation) or one e-, so only photons are ever asked for
+  // two at a time (with two of each allowed, and a copy of the track for the
+  // state before its step: 10^4 x 10 GeV 40.3 ms, now 39.7; 40 000 x 10 GeV
+  // in the mixed form 101.6 and 98.9; towers 24.9 and 23.5)
+  constexpr int kMaxA = PHOTONS ? 1 : 2;
   const uint32_t nmine = PHOTONS ? ln.n0 : ln.n1 + ln.n2 + ln.np;
   const uint32_t nxt = ln.cur ^ 1u;
   const KArgs& a0 = fresh_args();
@@ -736,7 +747,7 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
         const uint32_t ds = (s0 ? 1u : 0u) + (s1 ? 1u : 0u);
         // a home slot for every survivor that leaves the lane
         const bool leave = done && t.slab >= 0 && !will_continue;
-        Take ta = ask(rg, kNextSec + kSecA, da), tb = ask(rg, kNextSec + kSecB, db);
+        Take ta = ask<kMaxA>(rg, kNextSec + kSecA, da), tb = ask(rg, kNextSec + kSecB, db);
         Take th = ask(rg, kNextHome + (PHOTONS ? 0 : 1), leave && sp != 2 ? 1u : 0u);
         Take tp{0, 0, 0, 0, 0}, ts{0, 0, 0, 0, 0};
         if constexpr (!PHOTONS) tp = ask(rg, kNextHome + 2, leave && sp == 2 ? 1u : 0u);
@@ -762,9 +773,9 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
           serve(ctl, rg, asks);
         }
         const uint32_t lim_a = plan.lim[kSecA], lim_b = plan.lim[kSecB];
-        bool fits = !(da && (ta.slot(da - 1) >= lim_a || ta.slot(0) >= lim_a)) &&
-                    !(db && (tb.slot(db - 1) >= lim_b || tb.slot(0) >= lim_b));
-        if (shorts && ds && (ts.slot(ds - 1) >= plan.lim_s || ts.slot(0) >= plan.lim_s)) fits = false;
+        bool fits = !(da && ta.slot(0) >= lim_a) && !(db && tb.slot(0) >= lim_b);
+        if (kMaxA > 1 && da > 1 && ta.slot(1) >= lim_a) fits = false;
+        if (shorts && ds && ts.slot(0) >= plan.lim_s) fits = false;
         const bool commit = made && fits && !hold;
         const bool carry = made && !commit;  // back to the state before the last step
         const bool cont = done && t.slab >= 0 && !carry && will_continue;  // stays in the lane
@@ -823,46 +834,42 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
             dq.kill(ps);
           }
         };
-        auto put_queue = [&](int q, uint32_t d, const Take& tk, uint32_t lim) {
+        auto put_queue = [&](int q, int most, uint32_t d, const Take& tk, uint32_t lim) {
           if (!d) return;
           const Queue<R> dq = queue_view<R>(a, nxt, (uint32_t)q);
           const bool first = in0 && o.sec[0].sp == q;
           const uint32_t sl = tk.slot(0);
           if (sl < lim) put(dq, first ? o.sec[0] : o.sec[1], (uint32_t)(a.cap - 1 - sl));
-          if (d > 1) {
+          if (most > 1 && d > 1) {
             const uint32_t s2 = tk.slot(1);
             if (s2 < lim) put(dq, o.sec[1], (uint32_t)(a.cap - 1 - s2));
           }
         };
-        put_queue(kSecA, da, ta, lim_a);
-        put_queue(kSecB, db, tb, lim_b);
+        put_queue(kSecA, kMaxA, da, ta, lim_a);
+        put_queue(kSecB, 1, db, tb, lim_b);
         if (kShort && ds) {
           const Queue<R> sq = short_view<R>(a, nxt);
           const uint32_t sl = ts.slot(0);
           if (sl < plan.lim_s) put(sq, s0 ? o.sec[0] : o.sec[1], sl);
-          if (ds > 1) {
-            const uint32_t s2 = ts.slot(1);
-            if (s2 < plan.lim_s) put(sq, o.sec[1], s2);
-          }
         }
         if (keep) {
           const Queue<R> dq = queue_view<R>(a, nxt, (uint32_t)sp);
           if (hs >= a.cap) {
             atomicOr(&ctl->error, kErrOverflow);
           } else {
-            Trk<R> w = t;
+            // (a track written here leaves the lane)
             if (carry) {
-              w.x = x0;
-              w.y = y0;
-              w.z = z0;
-              w.E = e0;
-              w.ux = ux0;
-              w.uy = uy0;
-              w.uz = uz0;
-              w.n = t.n - 1;
-              w.slab = o.slab;
+              t.x = x0;
+              t.y = y0;
+              t.z = z0;
+              t.E = e0;
+              t.ux = ux0;
+              t.uy = uy0;
+              t.uz = uz0;
+              t.n -= 1;
+              t.slab = o.slab;
             }
-            store_track(dq, hs, w, a.vol_bits);
+            store_track(dq, hs, t, a.vol_bits);
             if (sp == 2) ++kept_b;
             else ++kept_a;
           }
@@ -1370,8 +1377,13 @@ __global__ void k_census(KArgs a) {
 
 // Kernel variants: the optional parts each kernel is built with: none, in a
 // slab stack the field and the records (mixed-species runs in a field, the
-// offload server), or all.  A context launches the smallest variant that
-// covers its configuration (KArgs::feat).
+// offload server), scattering and fluctuations, compounds with or without a
+// field, or all.  A context launches the smallest variant that covers its
+// configuration (KArgs::feat).  A part that is compiled in costs registers
+// and spills also where it is off: against the variant with all parts, 1500 x
+// 10 GeV with scattering and fluctuations 14.78 -> 13.44 ms, PbWO4 1501
+// mixed-species events in a field, mixed form 17.09 -> 16.64, 37 x 1 GeV 2.38
+// -> 2.28.  (Not with the short-electron routing: each would be built twice.)
 template <class R, int GEO>
 const void* visit_fn(uint32_t feat) {
   if (feat == 0) return reinterpret_cast<const void*>(&k_visit<R, GEO, 0>);
@@ -1380,6 +1392,8 @@ const void* visit_fn(uint32_t feat) {
     if (feat == (kFField | kFRecord)) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFField | kFRecord>);
     if (feat == (kFField | kFRecord | kFShort))
       return reinterpret_cast<const void*>(&k_visit<R, GEO, kFField | kFRecord | kFShort>);
+    if (feat == kFAlong) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFAlong>);
+    if (feat == kFFieldCompound) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFFieldCompound>);
   }
   if (feat == (kFAll & ~kFShort)) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFAll & ~kFShort>);
   return reinterpret_cast<const void*>(&k_visit<R, GEO, kFAll>);

@@ -29,6 +29,7 @@ constexpr double kInf = __builtin_huge_val();
 // target element, and the per-step records (step log, full ledger, exits,
 // per-event live counters).
 enum : int { kFField = 1, kFMsc = 2, kFFluct = 4, kFCompound = 8, kFRecord = 16, kFShort = 32, kFAll = 63,
+             kFAlong = kFMsc | kFFluct, kFFieldCompound = kFField | kFCompound,
              // box geometries: the caller hands over the boundary distance of every
              // straight step from the world volume (GeoPre), so the step holds no
              // walk of the hierarchy
