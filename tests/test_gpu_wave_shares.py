@@ -29,6 +29,22 @@ def test_histories_at_the_edges_of_the_wave_shares(E, oracle_mod, blocks, n):  #
     assert ledger_residual(got["edep"], got["ledger"], prim).max() < 1e-9
 
 
+@pytest.mark.parametrize("n", [256 + 2047, 256 + 2112, 9000, 20001])
+def test_index_chunks_by_what_is_left(E, oracle_mod, n):  # noqa: F811
+    """One block of four waves takes its queue's indices 64 at a time, by an
+    eighth of an even share of what is left, or 256 at a time: every track is
+    visited once (tallies of the oracle)."""
+    print(f"index chunks, {n} tracks", flush=True)
+    geo = I.calorimeter()
+    cfg = I.RunConfig(seed=29)
+    prim = I.random_tracks(n, 16, geo, 1e-3, 1.0, seed=n)
+    ref = oracle_mod.Oracle(geo, cfg).run(prim, n_events=16)
+    got = run_gpu(E, geo, cfg, prim, 16, flags=E.F_FULL_LEDGER, blocks=1)
+    for f in ("n_steps", "n_created", "n_null", "n_pair", "n_annih"):
+        assert np.array_equal(got["ledger"][f], ref["ledger"][f]), f
+    assert np.allclose(got["edep"], ref["edep"], rtol=1e-9, atol=1e-9)
+
+
 @pytest.mark.parametrize("n_bins,timing", [(40, False), (200, False), (200, True), (800, False)])
 def test_one_launch_for_both_species_or_one_each(E, oracle_mod, n_bins, timing):  # noqa: F811
     """One launch an iteration, two with per-kernel timing, two where the
