@@ -670,6 +670,7 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
   const auto within = [need_l](int parts) { return (need_l & ~(uint32_t)parts) == 0; };
   if (need_l == 0) a.feat = 0;
   else if (geo->n_boxes) a.feat = kAllParts;
+  else if (within(kFField) && !L.cap_s) a.feat = kFField;
   else if (within(kFField | kFRecord)) a.feat = kFField | kFRecord;
   else if (within(kFAlong) && !L.cap_s) a.feat = kFAlong;
   else if (within(kFFieldCompound) && !L.cap_s) a.feat = kFFieldCompound;

@@ -1378,14 +1378,14 @@ __global__ void k_census(KArgs a) {
 #endif  // EMS_SLAB_F32_TU
 
 // Kernel variants: the optional parts each kernel is built with: none, in a
-// slab stack the field and the records (mixed-species runs in a field, the
-// offload server), scattering and fluctuations, compounds with or without a
-// field, or all.  A context launches the smallest variant that covers its
+// slab stack the field, the field and the records (the offload server),
+// scattering and fluctuations, compounds with or without a field, or all.  A context launches the smallest variant that covers its
 // configuration (KArgs::feat).  A part that is compiled in costs registers
 // and spills also where it is off: against the variant with all parts, 1500 x
 // 10 GeV with scattering and fluctuations 14.78 -> 13.44 ms, PbWO4 1501
 // mixed-species events in a field, mixed form 17.09 -> 16.64, 37 x 1 GeV 2.38
-// -> 2.28.  (Not with the short-electron routing: each would be built twice.)
+// -> 2.28; against the field with the records 2500 mixed-species events 27.83
+// -> 26.42, 48 tracks 0.364 -> 0.343.  (Not with the short-electron routing: each would be built twice.)
 template <class R, int GEO>
 const void* visit_fn(uint32_t feat) {
   if (feat == 0) return reinterpret_cast<const void*>(&k_visit<R, GEO, 0>);
@@ -1394,6 +1394,7 @@ const void* visit_fn(uint32_t feat) {
     if (feat == (kFField | kFRecord)) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFField | kFRecord>);
     if (feat == (kFField | kFRecord | kFShort))
       return reinterpret_cast<const void*>(&k_visit<R, GEO, kFField | kFRecord | kFShort>);
+    if (feat == kFField) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFField>);
     if (feat == kFAlong) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFAlong>);
     if (feat == kFFieldCompound) return reinterpret_cast<const void*>(&k_visit<R, GEO, kFFieldCompound>);
   }
