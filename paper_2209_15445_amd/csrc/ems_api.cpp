@@ -806,7 +806,8 @@ ems_status ems_destroy(ems_ctx* c) {
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   for (hipEvent_t e : c->evk) (void)hipEventDestroy(e);
-  if (c->graph) (void)hipGraphExecDestroy(c->graph);
+  for (hipGraphExec_t g : c->graph)
+    if (g) (void)hipGraphExecDestroy(g);
   delete c;
   return EMS_OK;
 }
@@ -1220,10 +1221,12 @@ ems_status rt_enqueue_device(ems_ctx* c, const ems_primary* p, uint64_t n) {
   return EMS_OK;
 }
 
-// The kernels of one chunk: census, then K iterations (photon launch, e-/e+
-// launch), with a HIP event after every launch when timing (direct
-// launches only: events recorded inside a graph are not timeable here).
-// Returns the first error.
+// The kernels of one chunk: census, then K iterations (short launch with
+// short buffers, then one visit launch of both species or one of each), with
+// a HIP event after every launch when timing (direct launches only: events
+// recorded inside a graph are not timeable here).  Every iteration's launches
+// get the buffer it reads; args.cur is left at the next chunk's.  Returns the
+// first error.
 static hipError_t enqueue_chunk(ems_ctx* c, uint32_t K, bool timing) {
   hipError_t e = launch_census(c->args, c->stream);
   if (e == hipSuccess && timing) e = hipEventRecord(c->evk[0], c->stream);
@@ -1234,24 +1237,28 @@ static hipError_t enqueue_chunk(ems_ctx* c, uint32_t K, bool timing) {
     if (e == hipSuccess && timing) e = hipEventRecord(c->evk[3 * k + 2], c->stream);
     if (e == hipSuccess) e = launch_visit(c->args, c->args.split ? 2u : 3u, c->blocks_v, c->stream);
     if (e == hipSuccess && timing) e = hipEventRecord(c->evk[3 * k + 3], c->stream);
+    c->args.cur ^= 1u;
   }
   return e;
 }
 
 // Capture one chunk of K iterations as a graph.  The kernels read every
-// changing quantity from the device control block, so one graph serves all
-// chunks; it holds kernel nodes only (no memset or event nodes).
+// changing quantity but the starting buffer from the device control block, so
+// one graph serves all chunks that start with the same buffer; it holds
+// kernel nodes only (no memset or event nodes).
 static hipError_t capture_chunk(ems_ctx* c, uint32_t K) {
   hipGraph_t g = nullptr;
+  const uint32_t first = c->args.cur;
   hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed);
   if (e != hipSuccess) return e;
   const hipError_t el = enqueue_chunk(c, K, false);
+  c->args.cur = first;
   e = hipStreamEndCapture(c->stream, &g);
   if (el != hipSuccess) e = el;
-  if (e == hipSuccess) e = hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0);
+  if (e == hipSuccess) e = hipGraphInstantiate(&c->graph[first], g, nullptr, nullptr, 0);
   if (g) (void)hipGraphDestroy(g);
   if (e == hipSuccess) c->graph_k = K;
-  else c->graph = nullptr;
+  else c->graph[first] = nullptr;
   return e;
 }
 
@@ -1263,11 +1270,13 @@ ems_status rt_chunk(ems_ctx* c, uint32_t K) {
     c->evk.push_back(e);
   }
   bool graph = !timing && !(c->cfg.flags & EMS_F_NO_GRAPH) && c->stream != nullptr && !c->graph_off;
-  if (graph && c->graph && c->graph_k != K) {
-    HIPCHK(c, hipGraphExecDestroy(c->graph));
-    c->graph = nullptr;
+  for (hipGraphExec_t& g : c->graph) {
+    if (!graph || !g || c->graph_k == K) continue;
+    const hipGraphExec_t old = g;
+    g = nullptr;
+    HIPCHK(c, hipGraphExecDestroy(old));
   }
-  if (graph && !c->graph && capture_chunk(c, K) != hipSuccess) {
+  if (graph && !c->graph[c->args.cur] && capture_chunk(c, K) != hipSuccess) {
     // capture not available here: launch directly from now on
     (void)hipGetLastError();
     c->graph_off = true;
@@ -1276,7 +1285,8 @@ ems_status rt_chunk(ems_ctx* c, uint32_t K) {
   const bool span = c->ev0 != nullptr;  // contexts without allocations keep no events
   if (span) HIPCHK(c, hipEventRecord(c->ev0, c->stream));
   if (graph) {
-    HIPCHK(c, hipGraphLaunch(c->graph, c->stream));
+    HIPCHK(c, hipGraphLaunch(c->graph[c->args.cur], c->stream));
+    c->args.cur ^= K & 1u;
     c->stats.graph_launches += 1;
   } else {
     HIPCHK(c, enqueue_chunk(c, K, timing));

@@ -124,10 +124,24 @@ enum : int {
   kAddStepsShort = 16,  // steps of the short launch (in kAddSteps too)
   kAdds = 17
 };
+// The queues of one iteration, by buffer.  The launches of an iteration read
+// the record of the current buffer (KArgs::cur, alternating from iteration to
+// iteration) and its close writes the other one: a block may start after the
+// iteration was closed (another context's work may hold the device, or the
+// grid may exceed it) and still has to read what the blocks before it read.
+struct Extents {
+  uint32_t n_home[3];  // tracks in the home region
+  uint32_t n_sec[3];   // tracks in the secondary region
+  // Live records: the extents n_home + n_sec may include dead slots (unused
+  // ends of wave-private append chunks); n_real counts the live tracks.
+  uint32_t n_real[3];
+  // Short electrons (KArgs::short_E): extent and live records of the short
+  // buffer, and the spill counter before the iteration.
+  uint32_t n_short, n_short_real, spilled;
+  uint32_t stop;  // an error was seen: nothing is stepped any more
+};
 struct Ctl {
-  uint32_t cur;           // index of the current buffer (0/1)
-  uint32_t n_home[3];     // current queues: tracks in the home region
-  uint32_t n_sec[3];      // current queues: tracks in the secondary region
+  Extents ext[2];
   uint32_t blocks_done;   // completion ticket of the running launch
   uint32_t iteration;
   uint32_t live;          // tracks in the current queues (after the swap)
@@ -136,14 +150,7 @@ struct Ctl {
   unsigned long long steps[3], created[3], deferred, log_n;
   unsigned long long visits[3];  // track records loaded (one per visit)
   unsigned long long made_by[2];  // secondary records written (photon, e-/e+ launches)
-  // Live records: the extents n_home + n_sec may include dead slots (unused
-  // ends of wave-private append chunks); n_real counts the live tracks of
-  // the current queues.
-  uint32_t n_real[3];
   unsigned long long exit_n;  // outgoing tracks recorded (may exceed the capacity)
-  // Short electrons (KArgs::short_E): extent and live records of the
-  // current short buffer.
-  uint32_t n_short, n_short_real;
   unsigned long long steps_s;  // e- steps taken by the short launches
   // tallies of the running iteration, folded into the totals above when it
   // ends
@@ -154,8 +161,9 @@ struct Ctl {
   // 10^4 x 10 GeV 43.1 ms, 40 000 x 10 GeV in the mixed form 111.4, 500 x
   // 2 GeV 4.49; each in its own: 40.9, 104.5 and 4.27).
   // Append counters: home (0..2) and secondary regions (3..5) of the next
-  // queues by species, next short buffer (6), and this iteration's spill
-  // buffer (7: tracks the short launch hands to the e-/e+ loop).
+  // queues by species, next short buffer (6), and the spill buffer (7: tracks
+  // the short launch hands to the e-/e+ loop; never cleared during a batch,
+  // its slots count from Extents::spilled).
   alignas(128) uint32_t next[kNextCounters * kLine];
   alignas(128) uint32_t cursor[2 * kLine];  // queue indices handed out (photons, e-/e+)
 };
@@ -211,6 +219,7 @@ struct KArgs {
   uint32_t* profile;   // [profile_cap][3]
   int32_t* live_ev;    // [rows] live tracks per event (kFlagEventLive)
   uint64_t cap;        // tracks per species per buffer
+  uint32_t cur;        // this iteration's buffer and extents (0/1)
   uint64_t qstride;    // bytes of a queue buffer (cap records)
   uint32_t max_events;  // tally rows
   uint64_t log_cap;

@@ -19,17 +19,17 @@
 //  - secondaries are reserved against a per-species limit that always leaves
 //    room for every survivor; a track whose secondaries do not fit is carried
 //    from before that step, so a full queue defers work instead of losing it;
-//  - the last block of the launch swaps the queues, so a chain of
-//    launches needs no host round trip.
+//  - the last block of the launch leaves the extents of the next queues to
+//    the next launch, so a chain of launches needs no host round trip.
 #include <hip/hip_runtime.h>
 
-#include "ems_device.hpp"
+#include "ems_iteration.hpp"
 
 namespace ems {
 
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = 64 * kBlockWaves;
 // lanes waiting in the world volume that make a wave compute their boundary
 // distances together (box geometries)
 #ifndef EMS_WORLD_BATCH
@@ -415,7 +415,6 @@ struct DevSink {
 // Stage the table blocks of the launch's species (bit 0 of `which`: photons,
 // bit 1: e-/e+), the slab planes, slab materials and material constants in
 // LDS; returns the environment pointing there.
-enum : uint32_t { kPhotons = 1u, kLeptons = 2u };
 template <class R>
 __device__ inline R* stage_tables(const void* src, uint32_t n, char*& lds) {
   R* dst = reinterpret_cast<R*>(lds);
@@ -517,27 +516,6 @@ __device__ __forceinline__ StepEnv<R> env_of(const KArgs& a, const Staged<R>& st
 
 }  // namespace
 
-// How one species' tracks are dealt to `waves` of a launch's waves: `lanes`
-// lanes of a wave hold tracks, wave w of them starts with the queue indices
-// [first, first + lanes), and indices from `pool` on are handed out by the
-// launch's cursor.
-// A population that does not fill the device is dealt evenly over the waves:
-// what bounds such a launch is the chain of dependent steps of its slowest
-// wave, and a wave pays for every path that any of its lanes takes, so a wave
-// with one track runs its steps several times faster than one with 64.
-// 32 x 1 GeV (at most 6000 tracks at once, 2048 waves): 6.7 ms a batch with
-// 64 tracks to a wave, 3.2 ms dealt evenly.
-struct WaveShare {
-  uint32_t lanes, first, pool;
-};
-__device__ inline WaveShare wave_share(uint32_t n, uint32_t w, uint32_t waves) {
-  WaveShare s;
-  const uint32_t even = n / waves + (n % waves != 0);
-  s.lanes = even >= 64u ? 64u : (even > 1u ? even : 1u);
-  s.first = w * s.lanes;
-  s.pool = waves * s.lanes;
-  return s;
-}
 // The visits of one species in one iteration: photons (PHOTONS) or e-/e+.
 //
 // Batched lane refill: the lanes of a wave keep stepping their tracks while
@@ -577,7 +555,8 @@ constexpr int visit_waves() {
 // What the waves of a launch share: the current queues' sizes, the append
 // plan, and where the launch's tallies go.
 struct Launch {
-  uint32_t cur, h0, h1, h2, n0, n1, n2, np;
+  uint32_t cur;
+  Sizes z;
   Plan plan;
   unsigned long long* cnt;  // block's tallies (LDS)
 };
@@ -597,7 +576,7 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
   // state before its step: 10^4 x 10 GeV 40.3 ms, now 39.7; 40 000 x 10 GeV
   // in the mixed form 101.6 and 98.9; towers 24.9 and 23.5)
   constexpr int kMaxA = PHOTONS ? 1 : 2;
-  const uint32_t nmine = PHOTONS ? ln.n0 : ln.n1 + ln.n2 + ln.np;
+  const uint32_t nmine = PHOTONS ? ln.z.n0 : ln.z.n1 + ln.z.n2 + ln.z.np;
   const uint32_t nxt = ln.cur ^ 1u;
   const KArgs& a0 = fresh_args();
   const int max_visit = (int)(PHOTONS ? a0.photon_steps_per_visit : a0.steps_per_visit);
@@ -701,15 +680,15 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
         // (with fewer than 64 lanes a wave the first shares hold every track)
         drained = share.lanes < 64u || __ballot(want && i >= nmine) != 0;
         if (got) {
-          uint32_t idx = i, home = PHOTONS ? ln.h0 : ln.h1;
-          if (!PHOTONS && i >= ln.n1) {
+          uint32_t idx = i, home = PHOTONS ? ln.z.h0 : ln.z.h1;
+          if (!PHOTONS && i >= ln.z.n1) {
             nsp = 2;
-            idx = i - ln.n1;
-            home = ln.h2;
+            idx = i - ln.z.n1;
+            home = ln.z.h2;
           }
-          const bool spilled = !PHOTONS && (F & kFShort) && i >= ln.n1 + ln.n2;  // an e- from the spill buffer
+          const bool spilled = !PHOTONS && (F & kFShort) && i >= ln.z.n1 + ln.z.n2;  // an e- from the spill buffer
           if (spilled) nsp = 1;
-          const uint32_t pos = spilled ? i - ln.n1 - ln.n2 : queue_pos(idx, home, a.cap);
+          const uint32_t pos = spilled ? i - ln.z.n1 - ln.z.n2 : queue_pos(idx, home, a.cap);
           const Queue<R> src = spilled ? short_view<R>(a, 2u) : queue_view<R>(a, ln.cur, (uint32_t)nsp);
           nw = src.load(pos, nt);
         }
@@ -960,44 +939,51 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
 }
 
 // The last block of an iteration to end folds the tallies into the totals
-// and makes the next queues the current ones.  Wave 0 of that block does it,
-// a counter to a lane: every counter is fetched and cleared in one exchange
-// each (they live at the memory side, some microseconds a round trip; one
-// after another they took 9 us of every iteration).
+// and leaves the extents of the next queues to the next iteration.  Wave 0 of
+// that block does it, a counter to a lane: every counter is fetched and
+// cleared in one exchange each (they live at the memory side, some
+// microseconds a round trip; one after another they took 9 us of every
+// iteration).
 template <bool SHORT>
 __device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& ln) {
   const uint32_t lane = __lane_id();
-  uint32_t app = 0;
+  uint32_t app = 0, error = 0;
   unsigned long long add = 0;
-  if (lane < kNextCounters) app = atomicExch(&ctl->next[lane * kLine], 0u);
+  // (the spill counter is read only)
+  if (lane < kNextCounters) app = atomicAnd(&ctl->next[lane * kLine], lane == kNextSpill ? ~0u : 0u);
   if (lane < kAdds) add = atomicExch(&ctl->add[lane], 0ull);
+  if (lane == 0) error = atomicOr(&ctl->error, 0u);
   auto next_of = [&](int c) { return (uint32_t)__builtin_amdgcn_readlane((int)app, c); };
   auto add_of = [&](int k) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)add, k);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(add >> 32), k);
     return (unsigned long long)lo | ((unsigned long long)hi << 32);
   };
-  const uint32_t srv = SHORT ? (uint32_t)add_of(kAddMadeShort) : 0u;
-  uint32_t real[3], live = srv;
+  Appended n;
+  n.shorts_real = SHORT ? (uint32_t)add_of(kAddMadeShort) : 0u;
+  uint32_t live = n.shorts_real;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    real[q] = (uint32_t)(add_of(kAddMade + q) + add_of(kAddKept + q)) - (q == 1 ? srv : 0u);
-    live += real[q];
+    n.real[q] = (uint32_t)(add_of(kAddMade + q) + add_of(kAddKept + q)) - (q == 1 ? n.shorts_real : 0u);
+    live += n.real[q];
   }
-  uint32_t home[3], sec[3];
   unsigned long long tot[kAdds];
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    home[q] = next_of(kNextHome + q);
-    sec[q] = next_of(kNextSec + q);
+    n.home[q] = next_of(kNextHome + q);
+    n.sec[q] = next_of(kNextSec + q);
+    n.lim[q] = ln.plan.lim[q];
   }
 #pragma unroll
   for (int k = 0; k < kAdds; ++k) tot[k] = add_of(k);
-  const uint32_t shorts = SHORT ? next_of(kNextShort) : 0u;
+  n.shorts = SHORT ? next_of(kNextShort) : 0u;
+  n.lim_s = ln.plan.lim_s;
+  n.spilled = SHORT ? next_of(kNextSpill) : 0u;
   const unsigned long long commits = tot[kAddSteps] + tot[kAddSteps + 1] + tot[kAddSteps + 2];
   const unsigned long long carried = tot[kAddCarried];
   if (lane != 0) return;
-  const uint32_t r0 = ctl->n_real[0], r1 = ctl->n_real[1] + (SHORT ? ctl->n_short_real : 0u), r2 = ctl->n_real[2];
+  const Extents& e = ctl->ext[ln.cur];
+  const uint32_t r0 = e.n_real[0], r1 = e.n_real[1] + (SHORT ? e.n_short_real : 0u), r2 = e.n_real[2];
   if (a.flags & kFlagProfile) {
     if (ctl->iteration < a.profile_cap) {
       a.profile[(size_t)ctl->iteration * 3 + 0] = r0;
@@ -1006,14 +992,15 @@ __device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& l
     }
   }
   if (r0 + r1 + r2 > 0) ctl->iteration += 1;
-  if (carried > 0 && commits == 0) atomicOr(&ctl->error, kErrStall);  // nothing can move: queues too small
+  if (carried > 0 && commits == 0) {  // nothing can move: queues too small
+    atomicOr(&ctl->error, kErrStall);
+    error |= kErrStall;
+  }
+  // the other record (the next short buffer becomes the current one with it)
+  ctl->ext[ln.cur ^ 1u] = next_extents(n, live, error != 0 || e.stop);
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    // with no live track left the dead slots need no visit
-    ctl->n_home[q] = live ? home[q] : 0u;
-    ctl->n_sec[q] = live ? (sec[q] < ln.plan.lim[q] ? sec[q] : ln.plan.lim[q]) : 0u;
-    ctl->n_real[q] = real[q];
-    const uint32_t all = real[q] + (q == 1 ? srv : 0u);
+    const uint32_t all = n.real[q] + (q == 1 ? n.shorts_real : 0u);
     ctl->peak[q] = all > ctl->peak[q] ? all : ctl->peak[q];
     ctl->steps[q] += tot[kAddSteps + q];
     ctl->visits[q] += tot[kAddVisits + q];
@@ -1022,16 +1009,10 @@ __device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& l
   ctl->made_by[0] += tot[kAddMadeBy];
   ctl->made_by[1] += tot[kAddMadeBy + 1];
   ctl->deferred += carried;
-  if constexpr (SHORT) {
-    // the next short buffer becomes the current one
-    ctl->n_short = live ? (shorts < ln.plan.lim_s ? shorts : ln.plan.lim_s) : 0u;
-    ctl->n_short_real = srv;
-    ctl->steps_s += tot[kAddStepsShort];
-  }
+  if constexpr (SHORT) ctl->steps_s += tot[kAddStepsShort];
   ctl->live = live;
   ctl->cursor[0] = 0;
   ctl->cursor[kLine] = 0;
-  ctl->cur = ln.cur ^ 1u;
   ctl->blocks_done = 0;
 }
 
@@ -1058,40 +1039,24 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
   constexpr bool kShort = (F & kFShort) != 0;
   Launch ln;
   ln.cnt = cnt;
-  ln.cur = ctl->cur;
-  ln.h0 = ctl->n_home[0];
-  ln.h1 = ctl->n_home[1];
-  ln.h2 = ctl->n_home[2];
-  ln.n0 = ln.h0 + ctl->n_sec[0];
-  ln.n1 = ln.h1 + ctl->n_sec[1];
-  ln.n2 = ln.h2 + ctl->n_sec[2];
-  // the e-/e+ loop also takes the tracks the short launch spilled
-  const uint32_t np_raw = kShort ? ctl->next[kNextSpill * (int)kLine] : 0u;
-  ln.np = (uint64_t)np_raw < a.cap_p ? np_raw : (uint32_t)a.cap_p;
+  ln.cur = a.cur;
+  ln.z = sizes_of<kShort>(ctl, ln.cur, a.cap_p);
   // secondary slots per species that leave room for all survivors
-  ln.plan = append_plan<kShort>(a, ln.n0, ln.n1, ln.n2, kShort ? ctl->n_short : 0u);
-  const uint32_t ng = which & kPhotons ? ln.n0 : 0u, nl = which & kLeptons ? ln.n1 + ln.n2 + ln.np : 0u;
-  const uint32_t waves = gridDim.x * (kBlock / 64);
-  uint32_t wg = (uint32_t)((uint64_t)waves * ng / ((uint64_t)ng + nl + (ng + nl == 0u)));
-  if (ng) wg = wg < 1u ? 1u : wg;
-  if (nl) wg = wg < waves ? wg : waves - 1u;
-  // consecutive waves go to different blocks (and so CUs); the waves with a
-  // share come first, photons then e-/e+, and only their blocks take part:
-  // the others end at once, without a ticket below (an iteration without
-  // tracks, of which a chunk may hold a dozen: 10 us with 512 tickets)
+  ln.plan = append_plan<kShort>(a, ln.z.n0, ln.z.n1, ln.z.n2, ln.z.ns);
+  const bool stop = ctl->ext[ln.cur].stop != 0;
+  const uint32_t ng = which & kPhotons && !stop ? ln.z.n0 : 0u;
+  const uint32_t nl = which & kLeptons && !stop ? ln.z.n1 + ln.z.n2 + ln.z.np : 0u;
+  // consecutive waves go to different blocks (and so CUs)
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
-  const WaveShare sg = wave_share(ng, w, wg ? wg : 1u);
-  const uint32_t wl = waves - wg;
-  if (sg.lanes < 64u) wg = (ng + sg.lanes - 1) / sg.lanes;
-  const WaveShare sl = wave_share(nl, w - wg, wl ? wl : 1u);
-  const uint32_t used = wg + (sl.lanes < 64u ? (nl + sl.lanes - 1) / sl.lanes : wl);
-  const uint32_t workers = used < gridDim.x ? used : gridDim.x;
+  const Deal d = deal_launch(ng, nl, gridDim.x, w);
+  const WaveShare &sg = d.sg, &sl = d.sl;
+  const uint32_t workers = d.workers;
   if (blockIdx.x >= workers && (workers || blockIdx.x)) return;
-  if (workers && ctl->error == 0) {
+  if (workers) {
     clear_counts(cnt);
     const Staged<R> st = stage<R, GEO>(a, reinterpret_cast<char*>(lds_words), which);
     Ranges rg{};
-    const bool own_g = w < wg;
+    const bool own_g = w < d.wg;
 #pragma unroll 1
     for (int turn = 0; turn < 2; ++turn) {
       const bool photons = own_g == (turn == 0);
@@ -1168,15 +1133,14 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   char* lds = reinterpret_cast<char*>(lds_words);
   __shared__ unsigned long long cnt[kAdds];
   Ctl* ctl = a.ctl;
-  const uint32_t cur = ctl->cur;
-  const uint32_t ns = ctl->n_short;
-  if (blockIdx.x >= (ns + kBlock - 1) / kBlock || ctl->error != 0) return;
-  const uint32_t n0 = ctl->n_home[0] + ctl->n_sec[0], n1 = ctl->n_home[1] + ctl->n_sec[1];
-  const uint32_t n2 = ctl->n_home[2] + ctl->n_sec[2];
+  const uint32_t cur = a.cur;
+  const Sizes z = sizes_of<true>(ctl, cur, a.cap_p);
+  const uint32_t ns = z.ns, spilled = ctl->ext[cur].spilled;
+  if (blockIdx.x >= (ns + kBlock - 1) / kBlock || ctl->ext[cur].stop) return;
   clear_counts(cnt);
   const Staged<R> st = stage<R, GEO>(a, lds, kLeptons);
   const StepEnv<R> env = env_of<R, GEO>(a, st);
-  const Plan plan = append_plan<true>(a, n0, n1, n2, ns);
+  const Plan plan = append_plan<true>(a, z.n0, z.n1, z.n2, ns);
   DevSink sink;
   const bool track_live = (F & kFRecord) && (a.flags & kFlagEventLive) != 0;
   const Queue<R> src = short_view<R>(a, cur);
@@ -1243,7 +1207,7 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
       }
     }
     if (to_spill) {
-      const uint32_t ps = tp.slot(0);
+      const uint32_t ps = tp.slot(0) - spilled;
       if (ps >= a.cap_p) atomicOr(&ctl->error, kErrOverflow);
       else store_track(spill, ps, first, a.vol_bits);
     }
@@ -1254,7 +1218,9 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   for (uint32_t x = rg.lo[kNextHome + 1] + __lane_id(); x < rg.hi[kNextHome + 1]; x += 64) {
     if (x < a.cap) dst.kill(x);
   }
-  for (uint32_t x = rg.lo[kNextSpill] + __lane_id(); x < rg.hi[kNextSpill]; x += 64) {
+  // (counted from the range's start: the counter is not cleared, and may wrap)
+  for (uint32_t k = __lane_id(); k < rg.hi[kNextSpill] - rg.lo[kNextSpill]; k += 64) {
+    const uint32_t x = rg.lo[kNextSpill] + k - spilled;
     if (x < a.cap_p) spill.kill(x);
   }
   Tallies sums;
@@ -1296,7 +1262,8 @@ __global__ __launch_bounds__(kBlock) void k_atomic_probe(double* cells, uint64_t
 template <class R>
 __global__ __launch_bounds__(kBlock) void k_inject(KArgs a, const InjRec* rec, uint32_t n) {
   Ctl* ctl = a.ctl;
-  const uint32_t cur = ctl->cur;
+  const uint32_t cur = a.cur;
+  Extents& e = ctl->ext[cur];
   for (uint32_t base = blockIdx.x * kBlock; base < n; base += gridDim.x * kBlock) {
     const uint32_t i = base + threadIdx.x;
     const bool active = i < n;
@@ -1304,9 +1271,9 @@ __global__ __launch_bounds__(kBlock) void k_inject(KArgs a, const InjRec* rec, u
     if (active) r = rec[i];
     for (int qs = 0; qs < 3; ++qs) {
       const uint32_t cnt = (active && (int)r.sp == qs) ? 1u : 0u;
-      const uint32_t slot = wave_reserve(&ctl->n_home[qs], cnt);
-      const bool fits = cnt && slot + ctl->n_sec[qs] < a.cap;
-      wave_count(&ctl->n_real[qs], fits ? 1u : 0u);
+      const uint32_t slot = wave_reserve(&e.n_home[qs], cnt);
+      const bool fits = cnt && slot + e.n_sec[qs] < a.cap;
+      wave_count(&e.n_real[qs], fits ? 1u : 0u);
       if (!cnt) continue;
       if (!fits) {
         atomicOr(&ctl->error, kErrOverflow);
@@ -1361,17 +1328,20 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(KArgs a, const uint32_t*
   }
 }
 
-// live count after injection (one thread)
+// live count after injection (one thread); after an injection that did not
+// fit nothing is stepped
 __global__ void k_census(KArgs a) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     Ctl* c = a.ctl;
-    uint32_t live = c->n_short_real;
+    Extents& e = c->ext[a.cur];
+    uint32_t live = e.n_short_real;
     for (int q = 0; q < 3; ++q) {
-      const uint32_t n = c->n_real[q] + (q == 1 ? c->n_short_real : 0u);
+      const uint32_t n = e.n_real[q] + (q == 1 ? e.n_short_real : 0u);
       c->peak[q] = n > c->peak[q] ? n : c->peak[q];
-      live += c->n_real[q];
+      live += e.n_real[q];
     }
     c->live = live;
+    if (c->error) e.stop = 1;
   }
 }
 

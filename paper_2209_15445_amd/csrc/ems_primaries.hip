@@ -209,8 +209,9 @@ __global__ __launch_bounds__(kIdGroup) void k_few_primaries(KArgs a, const PrimR
   if (!room) return;
   group_ids(s, in, q.event, row_next, [&](uint32_t pos, unsigned long long id) { ids[pos] = id; });
   Ctl* ctl = a.ctl;
-  const uint32_t cur = ctl->cur;
-  const uint32_t home = in ? ctl->n_home[sp] : 0u, sec = in ? ctl->n_sec[sp] : 0u;
+  const uint32_t cur = a.cur;
+  Extents& e = ctl->ext[cur];
+  const uint32_t home = in ? e.n_home[sp] : 0u, sec = in ? e.n_sec[sp] : 0u;
   if (in) {
     const InjRec r = staged(a, q, keys);
     const uint32_t slot = home + rank;
@@ -230,13 +231,13 @@ __global__ __launch_bounds__(kIdGroup) void k_few_primaries(KArgs a, const PrimR
       tr.slab = r.slab;
       queue_view<R>(a, cur, sp).store(slot, tr, (uint32_t)r.slab);
       if (a.flags & kFlagEventLive) atomicAdd(&a.live_ev[r.ev], 1);
-      atomicAdd(&ctl->n_real[sp], 1u);
+      atomicAdd(&e.n_real[sp], 1u);
     } else {
       atomicOr(&ctl->error, kErrOverflow);
     }
   }
   __syncthreads();  // (all have read the extents)
-  if (t < 3) ctl->n_home[t] += t == 0 ? total[0] : (t == 1 ? total[1] : total[2]);
+  if (t < 3) e.n_home[t] += t == 0 ? total[0] : (t == 1 ? total[1] : total[2]);
 }
 
 // Restart of a batch: the tallies to zero, and the control block but for the
@@ -247,7 +248,7 @@ struct Spans {
   uint4* p[3];
   uint64_t n[3];  // 16-byte words
 };
-__global__ __launch_bounds__(kBlock) void k_restart(Ctl* ctl, Spans z) {
+__global__ __launch_bounds__(kBlock) void k_restart(Ctl* ctl, uint32_t cur, Spans z) {
   const uint64_t stride = (uint64_t)gridDim.x * kBlock;
 #pragma unroll
   for (int k = 0; k < 3; ++k)
@@ -255,30 +256,16 @@ __global__ __launch_bounds__(kBlock) void k_restart(Ctl* ctl, Spans z) {
       z.p[k][i] = make_uint4(0u, 0u, 0u, 0u);
   if (blockIdx.x) return;
   static_assert(sizeof(Ctl) % 4 == 0, "cleared by words");
-  uint32_t cur = 0, home[3], sec[3], real[3], ns = 0, nsr = 0;
+  Extents e{};
   if (threadIdx.x == 0) {
-    cur = ctl->cur;
-    for (int q = 0; q < 3; ++q) {
-      home[q] = ctl->n_home[q];
-      sec[q] = ctl->n_sec[q];
-      real[q] = ctl->n_real[q];
-    }
-    ns = ctl->n_short;
-    nsr = ctl->n_short_real;
+    e = ctl->ext[cur];
+    e.spilled = 0;
+    e.stop = 0;
   }
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += kBlock) reinterpret_cast<uint32_t*>(ctl)[i] = 0u;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    ctl->cur = cur;
-    for (int q = 0; q < 3; ++q) {
-      ctl->n_home[q] = home[q];
-      ctl->n_sec[q] = sec[q];
-      ctl->n_real[q] = real[q];
-    }
-    ctl->n_short = ns;
-    ctl->n_short_real = nsr;
-  }
+  if (threadIdx.x == 0) ctl->ext[cur] = e;
 }
 
 // Rows to memory of the host, a block to a row at a time: deposits as they
@@ -353,7 +340,7 @@ hipError_t launch_restart(const KArgs& a, const Span (&z)[3], hipStream_t s) {
   }
   const uint64_t want = (words + kBlock - 1) / kBlock;
   const uint32_t blocks = (uint32_t)(want < 4096 ? want : 4096);
-  hipLaunchKernelGGL(k_restart, dim3(blocks), dim3(kBlock), 0, s, a.ctl, v);
+  hipLaunchKernelGGL(k_restart, dim3(blocks), dim3(kBlock), 0, s, a.ctl, a.cur, v);
   return hipGetLastError();
 }
 hipError_t launch_read_rows(const KArgs& a, uint32_t first, uint32_t n, double* edep, LedgerDev* led, hipStream_t s) {

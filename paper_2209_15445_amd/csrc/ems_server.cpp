@@ -144,7 +144,8 @@ void ems_server::run() {
       fail_all(std::string("device loop failed: ") + ems_last_error());
       return;
     }
-    for (int s2 = 0; s2 < 3; ++s2) occupied[s2] = ctx->pin_ctl->n_home[s2] + ctx->pin_ctl->n_sec[s2];
+    const Extents& left = ctx->pin_ctl->ext[ctx->args.cur];
+    for (int s2 = 0; s2 < 3; ++s2) occupied[s2] = left.n_home[s2] + left.n_sec[s2];
     if (rt_read_live(ctx, live.data())) {
       fail_all(std::string("live counters unreadable: ") + ems_last_error());
       return;
