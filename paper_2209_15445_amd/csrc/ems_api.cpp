@@ -609,13 +609,14 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
   c->device = dev;
   const uint64_t nodes = cfg->n_bins + 1;
   const uint32_t staged = geo->n_boxes ? 0u : geo->n_slabs;  // box geometries keep planes and materials global
-  const uint32_t common = (uint32_t)((geo->n_boxes ? 0u : staged + 1) * 8 + geo->n_materials * sizeof(MatRT) + staged * 4 + 64);
+  const uint32_t common = (uint32_t)((geo->n_boxes ? 0u : staged + 1) * 8 + geo->n_materials * sizeof(MatRT) + staged * 4);
   const uint64_t rb = real_bytes(cfg);
   const uint64_t gbytes = (geo->n_materials * kGammaTables * nodes * rb + 7) / 8 * 8;
   const uint64_t lbytes = (geo->n_materials * kLeptonTables * nodes * rb + 7) / 8 * 8;
   const uint32_t lds_g = (uint32_t)gbytes + common;
   const uint32_t lds_l = (uint32_t)lbytes + common;
-  if (lds_l > 160u * 1024u) return bad(fail(EMS_E_INVALID, "tables exceed LDS"));
+  // (72 bytes before them hold a block's tallies)
+  if (lds_l + 64u > 160u * 1024u) return bad(fail(EMS_E_INVALID, "tables exceed LDS"));
 
   KArgs& a = c->args;
   a.qbase = c->ws + L.queues;

@@ -278,13 +278,21 @@ __device__ inline void wave_count(uint32_t* counter, uint32_t v) {
 
 // Launch tallies (Ctl::add): a wave sums each over its lanes, lane k keeps
 // tally k, and they are added to the block's copy in LDS with one instruction;
-// the block adds its copy to the launch's with another when it ends.  (Where
+// the block adds its copy to the launch's with another when it ends.  (The
+// copy is of 32-bit words, as tables may fill LDS but for 80 bytes: a wave
+// adds a sum that eight of could pass them, four waves with two loops each, to
+// the launch's tally itself.)  (Where
 // every lane adds to the same words the compiler sums them itself, one lane
 // after another: some 5000 instructions at the end of each of a wave's loops.
 // 300 requests 13.6 -> 12.6 ms, 32 x 1 GeV 1.80 -> 1.69, 500 x 2 GeV 4.07 ->
 // 3.98, 10^4 x 10 GeV 40.55 -> 40.37.)
-__device__ inline void clear_counts(unsigned long long* cnt) {
-  if (threadIdx.x < kAdds) cnt[threadIdx.x] = 0ull;
+__device__ inline void clear_counts(uint32_t* cnt) {
+  if (threadIdx.x < kAdds) cnt[threadIdx.x] = 0u;
+}
+// (the old value is waited for, so the addition is done)
+__device__ inline void add_tally(Ctl* ctl, uint32_t k, unsigned long long v) {
+  const unsigned long long old = atomicAdd(&ctl->add[k], v);
+  asm volatile("" ::"v"((uint32_t)old));
 }
 // sum over a wave with all lanes active: within rows of 16 lanes, then the
 // rows' totals (row_shr 1, 2, 4, 8; row_bcast 15 and 31)
@@ -304,20 +312,19 @@ struct Tallies {
     const unsigned long long s = wave_total(v & 0xFFFFu) + ((unsigned long long)wave_total(v >> 16) << 16);
     if (__lane_id() == (uint32_t)k) mine = s;
   }
-  __device__ void add_to(unsigned long long* cnt) const {
-    if (__lane_id() < kAdds && mine) atomicAdd(&cnt[__lane_id()], mine);
+  __device__ void add_to(Ctl* ctl, uint32_t* cnt) const {
+    static_assert(2 * kBlockWaves <= 8, "eight sums below 2^29 fit a word");
+    if (__lane_id() >= kAdds || !mine) return;
+    if (mine >> 29) add_tally(ctl, __lane_id(), mine);
+    else atomicAdd(&cnt[__lane_id()], (uint32_t)mine);
   }
 };
 // all waves of the block have counted (a barrier inside)
-__device__ inline void publish_counts(Ctl* ctl, const unsigned long long* cnt) {
+__device__ inline void publish_counts(Ctl* ctl, const uint32_t* cnt) {
   __syncthreads();
   if (threadIdx.x < kAdds) {
-    const unsigned long long v = cnt[threadIdx.x];
-    // (the old value is waited for, so the addition is done)
-    if (v) {
-      const unsigned long long old = atomicAdd(&ctl->add[threadIdx.x], v);
-      asm volatile("" ::"v"((uint32_t)old));
-    }
+    const uint32_t v = cnt[threadIdx.x];
+    if (v) add_tally(ctl, threadIdx.x, v);
   }
 }
 
@@ -558,7 +565,7 @@ struct Launch {
   uint32_t cur;
   Sizes z;
   Plan plan;
-  unsigned long long* cnt;  // block's tallies (LDS)
+  uint32_t* cnt;  // block's tallies (LDS)
 };
 
 template <bool PHOTONS, class R, int GEO, int F>
@@ -935,7 +942,7 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
   sums.count(kAddMadeBy + kOwn, made_a + made_b + made_s);
   sums.count(kAddCarried, carried_n);
   if constexpr (kShort) sums.count(kAddMadeShort, made_s);
-  sums.add_to(ln.cnt);
+  sums.add_to(ctl, ln.cnt);
 }
 
 // The last block of an iteration to end folds the tallies into the totals
@@ -1034,7 +1041,7 @@ __device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& l
 template <class R, int GEO, int F>
 __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KArgs a, uint32_t which) {
   extern __shared__ double lds_words[];
-  __shared__ unsigned long long cnt[kAdds];
+  __shared__ uint32_t cnt[kAdds];
   Ctl* ctl = a.ctl;
   constexpr bool kShort = (F & kFShort) != 0;
   Launch ln;
@@ -1131,7 +1138,7 @@ template <class R, int GEO, int F>
 __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KArgs a) {
   extern __shared__ double lds_words[];
   char* lds = reinterpret_cast<char*>(lds_words);
-  __shared__ unsigned long long cnt[kAdds];
+  __shared__ uint32_t cnt[kAdds];
   Ctl* ctl = a.ctl;
   const uint32_t cur = a.cur;
   const Sizes z = sizes_of<true>(ctl, cur, a.cap_p);
@@ -1228,7 +1235,7 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   sums.count(kAddStepsShort, steps);
   sums.count(kAddVisits + 1, loads);
   sums.count(kAddKept + 1, kept);
-  sums.add_to(cnt);
+  sums.add_to(ctl, cnt);
   publish_counts(ctl, cnt);
 }
 
