@@ -566,6 +566,23 @@ ems_status ems_debug_host_transport(const ems_config* cfg, const ems_geometry* g
                                    const uint32_t* keys, double* edep, ems_ledger* ledger,
                                    ems_step_record* log, uint64_t log_cap, uint64_t* log_n);
 
+/* Test hook, never used by ems_run (section 3's step arithmetic on the GPU):
+ * evaluates one of the step's elementary functions on the device for n
+ * arguments.  d_a, d_b (second arguments of the quotients, else ignored) and
+ * d_out: n doubles each in device memory; queued on hip_stream.
+ * EMS_E_INVALID for an unknown function or null pointers. */
+enum {
+  EMS_MATH_LOG = 0,          /* ln a                                         */
+  EMS_MATH_EXP = 1,          /* e^a                                          */
+  EMS_MATH_SIN_TURN = 2,     /* sin 2 pi a                                   */
+  EMS_MATH_COS_TURN = 3,     /* cos 2 pi a                                   */
+  EMS_MATH_SQRT = 4,         /* square root of a                             */
+  EMS_MATH_QUOTIENT = 5,     /* a / b                                        */
+  EMS_MATH_QUOTIENT_F32 = 6  /* a / b of both rounded to single precision    */
+};
+ems_status ems_debug_device_math(uint32_t function, uint64_t n, const double* d_a, const double* d_b,
+                                 double* d_out, void* hip_stream);
+
 #ifdef __cplusplus
 }
 #endif

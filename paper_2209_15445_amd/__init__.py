@@ -147,6 +147,7 @@ def lib():
             "ems_server_destroy": [vp],
             "ems_server_drive": [vp, vp, vp, u32, u32, C.POINTER(C.c_double), C.POINTER(u64)],
             "ems_probe_atomics": [vp, u64, u64, vp, C.POINTER(C.c_double)],
+            "ems_debug_device_math": [u32, u64, vp, vp, vp, vp],
         }
         for name, args in sig.items():
             f = getattr(L, name)
@@ -430,6 +431,23 @@ def probe_atomics(cells, n_ops, stream=None):
     _check(lib().ems_probe_atomics(C.c_void_p(cells.data_ptr()), cells.numel(), int(n_ops),
                                    C.c_void_p(s.cuda_stream), C.byref(ms)))
     return ms.value
+
+
+MATH_FUNCTIONS = ("log", "exp", "sin_turn", "cos_turn", "sqrt", "quotient", "quotient_f32")
+
+
+def debug_device_math(function, a, b=None):
+    """One of MATH_FUNCTIONS of the step code on the device, element by element
+    of float64 CUDA tensors (test hook)."""
+    import torch
+    for t in (a,) if b is None else (a, b):
+        if not (t.is_cuda and t.dtype == torch.float64 and t.is_contiguous() and t.numel() == a.numel()):
+            raise ValueError("arguments must be contiguous float64 device tensors of one size")
+    out = torch.empty_like(a)
+    _check(lib().ems_debug_device_math(MATH_FUNCTIONS.index(function), a.numel(), C.c_void_p(a.data_ptr()),
+                                       None if b is None else C.c_void_p(b.data_ptr()), C.c_void_p(out.data_ptr()),
+                                       C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    return out
 
 
 class Server:

@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libems.so")
-SOURCES = ["ems_kernels.hip", "ems_primaries.hip", "ems_static.hip", "ems_api.cpp", "ems_tables.cpp", "ems_server.cpp", "ems_geometry.cpp"]
+SOURCES = ["ems_kernels.hip", "ems_primaries.hip", "ems_math_probe.hip", "ems_static.hip", "ems_api.cpp", "ems_tables.cpp", "ems_server.cpp", "ems_geometry.cpp"]
 # Compiled on its own with SLAB_F32_FLAGS, then linked with the rest: the
 # mixed-form slab-stack kernels, scheduled for instruction-level parallelism
 # (4% shorter mixed e-/e+ launches on the 10^5-event beam; the same setting

@@ -442,6 +442,16 @@ ems_status ems_probe_atomics(void* d_cells, uint64_t n_cells, uint64_t n_ops, vo
   return EMS_OK;
 }
 
+ems_status ems_debug_device_math(uint32_t function, uint64_t n, const double* d_a, const double* d_b, double* d_out,
+                                 void* stream) {
+  if (function > EMS_MATH_QUOTIENT_F32) return fail(EMS_E_INVALID, "unknown function");
+  if (!d_a || !d_out || (!d_b && function >= EMS_MATH_QUOTIENT)) return fail(EMS_E_INVALID, "null pointer");
+  if (n == 0) return EMS_OK;
+  if (launch_math(function, n, d_a, d_b, d_out, static_cast<hipStream_t>(stream)) != hipSuccess)
+    return fail(EMS_E_DEVICE, "launch failed");
+  return EMS_OK;
+}
+
 const char* ems_last_error(void) { return g_err.c_str(); }
 
 ems_status ems_workspace_bytes(const ems_config* cfg, const ems_geometry* geo, uint64_t* bytes) {

@@ -8,9 +8,10 @@
 // 25 and 41.  They are for finite positive normal arguments (log), arguments
 // whose exponential is in range or near it (exp) and fractions of a turn in
 // [0, 1] (sincos), which is all the step code asks of them.  Largest errors
-// on the device against long double, 1.7e7 arguments each: log 0.56 units in
-// the last place (the library's 0.65), exp 0.77 (0.88), sine and cosine of a
-// turn 1.5e-16 absolute (the library's, of the rounded angle, 7.0e-16).
+// on the device against long double (test_gpu_device_math.py prints them; 2 to
+// 4 million arguments each): log 0.55 units in the last place (the library's
+// 0.65), exp 0.73 (0.88), sine and cosine of a turn 1.4e-16 absolute (the
+// library's, of the rounded angle, 7.0e-16).
 //
 // Coefficients: minimax polynomials from the Remez exchange algorithm in
 // 60-digit arithmetic; the constants are rounded to double afterwards.
@@ -121,11 +122,14 @@ EMS_HD void sincos_turn(double u, double* sn, double* cs) {
   *cs = ((n + 1) & 2) ? -y : y;
 }
 
-// square root of zero or a positive normal number, and quotients of numbers
-// whose magnitudes are far from the ends of the range: the compiler's own
+// square root, and quotients of numbers whose magnitudes are far from the ends
+// of the range (2^+-400, in single precision 2^+-50): the compiler's own
 // sequences without the scaling that the ends need (22 and 11 instructions,
 // here 13 and 8; a further quotient by the same divisor 3 to 5), so the
-// results are the correctly rounded ones
+// results are the correctly rounded ones.  The root's are from 2^-968 up, and
+// zero's and infinity's; below, where its last residual is rounded, it is
+// within a unit in the last place down to the smallest normal number and keeps
+// 40 bits below that.
 #if defined(__HIP_DEVICE_COMPILE__)
 EMS_HD double plain_sqrt(double v) {
   const double y = __builtin_amdgcn_rsq(v);
@@ -135,7 +139,7 @@ EMS_HD double plain_sqrt(double v) {
   h = __builtin_fma(h, e, h);
   g = __builtin_fma(__builtin_fma(-g, g, v), h, g);
   g = __builtin_fma(__builtin_fma(-g, g, v), h, g);
-  return v == 0.0 ? v : g;
+  return __builtin_amdgcn_class(v, 0x260) ? v : g;  // (zeros and infinity)
 }
 template <class R>
 struct Recip;
