@@ -138,6 +138,7 @@ struct Extents {
   // Short electrons (KArgs::short_E): extent and live records of the short
   // buffer, and the spill counter before the iteration.
   uint32_t n_short, n_short_real, spilled;
+  uint32_t held;  // octaves held back: kNoLevel less the energy level (ems_iteration.hpp)
   uint32_t stop;  // an error was seen: nothing is stepped any more
 };
 struct Ctl {

@@ -181,18 +181,7 @@ __device__ inline void serve(Ctl* ctl, Ranges& rg, const Ask (&a)[N]) {
 struct Plan {
   uint32_t lim[3], chunk[3];
   uint32_t lim_s, chunk_s;  // appends to the next short buffer
-  // Photons wait this iteration: less than an eighth of the e- queue is free.
-  // Photons fill an e- queue to its last slot, and one that holds nothing
-  // but e- whose next step needs a slot for a Moller electron never moves
-  // again; the last eighth is left to the e-/e+, whose secondaries mostly end
-  // in their first steps.  (While the photon queue is less than half full: a
-  // full one would hold up bremsstrahlung.)  Queues that hold the whole
-  // shower never come to this.
-  bool hold;
 };
-__device__ inline bool photons_wait(const KArgs& a, uint64_t n0, uint64_t room_e) {
-  return room_e < a.cap / 8 && n0 < a.cap / 2;
-}
 // The current short electrons (ns) may all survive their first step into
 // the next e- queue, so they count with the current e- tracks; the short
 // launch's waves also append to that queue's home region.  New short
@@ -205,7 +194,8 @@ __device__ inline bool photons_wait(const KArgs& a, uint64_t n0, uint64_t room_e
 // SHORT: the kernel variant routes short electrons (the plan is the same
 // as without when the context has no short buffers).
 template <bool SHORT>
-__device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t ns) {
+__device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t ns,
+                                   uint32_t level) {
   Plan p;
   if constexpr (!SHORT) {
 #pragma unroll
@@ -217,11 +207,11 @@ __device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uin
       uint32_t chunk = EMS_APPEND_CHUNK;
       while (chunk > 1 && waves * chunk > budget) chunk >>= 1;
       p.chunk[q] = chunk;
-      p.lim[q] = (uint32_t)(room - (chunk > 1 ? (uint64_t)a.waves * chunk : 0));  // slack <= room / 4
+      const uint64_t slack = chunk > 1 ? (uint64_t)a.waves * chunk : 0;  // <= room / 4
+      p.lim[q] = secondary_limit((uint32_t)(room - slack), a.cap, level);
     }
     p.lim_s = 0;
     p.chunk_s = 1;
-    p.hold = photons_wait(a, n0, p.lim[1]);
     return p;
   }
   const uint64_t waves = 2ull * a.waves + (a.cap_s ? a.waves_s : 0u);
@@ -235,12 +225,11 @@ __device__ inline Plan append_plan(const KArgs& a, uint32_t n0, uint32_t n1, uin
     const uint64_t home_waves = (uint64_t)a.waves + (q == 1 && a.cap_s ? a.waves_s : 0u);
     const uint64_t slack = chunk > 1 ? home_waves * chunk : 0;
     p.chunk[q] = chunk;
-    p.lim[q] = (uint32_t)(room > slack ? room - slack : 0);
+    p.lim[q] = secondary_limit((uint32_t)(room > slack ? room - slack : 0), a.cap, level);
   }
   uint32_t cs = p.chunk[1];
   while (cs > 1 && waves * cs > a.cap_s / 4) cs >>= 1;
   p.chunk_s = cs;
-  p.hold = photons_wait(a, n0, p.lim[1]);
   p.lim_s = 0;
   if (a.cap_s) {
     const uint32_t half = p.lim[1] / 2;
@@ -726,7 +715,15 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
         // secondaries into the top regions (a step commits only if all of
         // its secondaries fit), then survivors or carried tracks
         // e- secondaries below short_E go to the next short buffer
-        const bool made = done && o.nsec > 0, hold = PHOTONS && plan.hold;
+        const bool made = done && o.nsec > 0;
+        bool hold = false;
+        if (ln.z.level < kNoLevel) {  // scarce room
+          const auto into = [&](int q) { return o.sec[0].sp == q || (o.nsec > 1 && o.sec[1].sp == q); };
+          const bool a_tight = tight(plan.lim[kSecA] + (kShort && kSecA == kElectron ? plan.lim_s : 0u), a.cap);
+          const bool b_tight = tight(plan.lim[kSecB] + (kShort && kSecB == kElectron ? plan.lim_s : 0u), a.cap);
+          hold = made && ((a_tight && into(kSecA)) || (b_tight && into(kSecB))) &&
+                 (float)e0 + (sp == 2 ? (float)(2.0 * kMe) : 0.0f) > energy_limit(ln.z.level);
+        }
         const bool s0 = shorts && made && !hold && o.sec[0].sp == kElectron && o.sec[0].E < a.short_E;
         const bool s1 = shorts && made && !hold && o.nsec > 1 && o.sec[1].sp == kElectron && o.sec[1].E < a.short_E;
         const bool in0 = made && !hold && !s0, in1 = made && !hold && o.nsec > 1 && !s1;  // to the queues
@@ -999,12 +996,24 @@ __device__ inline void close_iteration(const KArgs& a, Ctl* ctl, const Launch& l
     }
   }
   if (r0 + r1 + r2 > 0) ctl->iteration += 1;
-  if (carried > 0 && commits == 0) {  // nothing can move: queues too small
+  if (carried > 0 && commits == 0 && ln.z.level >= kNoLevel) {  // nothing can move: queues too small
     atomicOr(&ctl->error, kErrStall);
     error |= kErrStall;
   }
+  // how scarce room is (next_level)
+  uint64_t least = a.cap;
+  bool little = true;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const uint32_t lim = n.lim[q] + (SHORT && q == 1 ? n.lim_s : 0u);
+    const uint64_t used = (uint64_t)n.real[q] + (SHORT && q == 1 ? n.shorts_real : 0u);
+    const uint64_t room = used < a.cap ? a.cap - used : 0;
+    least = room < least ? room : least;
+    if (tight(lim, a.cap)) little = little && tot[kAddMade + q] * 4 <= lim;
+  }
+  const uint32_t level = next_level(ln.z.level, carried, commits, least, a.cap, little);
   // the other record (the next short buffer becomes the current one with it)
-  ctl->ext[ln.cur ^ 1u] = next_extents(n, live, error != 0 || e.stop);
+  ctl->ext[ln.cur ^ 1u] = next_extents(n, live, level, error != 0 || e.stop);
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     const uint32_t all = n.real[q] + (q == 1 ? n.shorts_real : 0u);
@@ -1049,7 +1058,7 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
   ln.cur = a.cur;
   ln.z = sizes_of<kShort>(ctl, ln.cur, a.cap_p);
   // secondary slots per species that leave room for all survivors
-  ln.plan = append_plan<kShort>(a, ln.z.n0, ln.z.n1, ln.z.n2, ln.z.ns);
+  ln.plan = append_plan<kShort>(a, ln.z.n0, ln.z.n1, ln.z.n2, ln.z.ns, ln.z.level);
   const bool stop = ctl->ext[ln.cur].stop != 0;
   const uint32_t ng = which & kPhotons && !stop ? ln.z.n0 : 0u;
   const uint32_t nl = which & kLeptons && !stop ? ln.z.n1 + ln.z.n2 + ln.z.np : 0u;
@@ -1147,7 +1156,7 @@ __global__ __launch_bounds__(kBlock, (short_waves<R, GEO, F>())) void k_short(KA
   clear_counts(cnt);
   const Staged<R> st = stage<R, GEO>(a, lds, kLeptons);
   const StepEnv<R> env = env_of<R, GEO>(a, st);
-  const Plan plan = append_plan<true>(a, z.n0, z.n1, z.n2, ns);
+  const Plan plan = append_plan<true>(a, z.n0, z.n1, z.n2, ns, z.level);
   DevSink sink;
   const bool track_live = (F & kFRecord) && (a.flags & kFlagEventLive) != 0;
   const Queue<R> src = short_view<R>(a, cur);

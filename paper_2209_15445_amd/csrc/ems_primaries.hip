@@ -261,6 +261,7 @@ __global__ __launch_bounds__(kBlock) void k_restart(Ctl* ctl, uint32_t cur, Span
     e = ctl->ext[cur];
     e.spilled = 0;
     e.stop = 0;
+    e.held = 0;
   }
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += kBlock) reinterpret_cast<uint32_t*>(ctl)[i] = 0u;

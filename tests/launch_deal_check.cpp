@@ -42,7 +42,7 @@ struct Run {
     next.spilled = SHORT ? ctl->next[kNextSpill * (int)kLine] : 0u;
     uint32_t live = next.shorts_real;
     for (uint32_t r : next.real) live += r;
-    ctl->ext[cur ^ 1u] = next_extents(next, live, 0);
+    ctl->ext[cur ^ 1u] = next_extents(next, live, kNoLevel, 0);
     if (one_record) ctl->ext[cur] = ctl->ext[cur ^ 1u];
     ctl->cursor[0] = ctl->cursor[kLine] = 0;
     ctl->blocks_done = 0;
@@ -150,6 +150,31 @@ long iterations(bool one_record, long* late) {
   return r.faults;
 }
 
+// the limits of scarce room: a free slot may be taken, an iteration leaves
+// some room while more than two are free, nothing is limited without a level,
+// and where nothing moves the level is soon gone
+long limits() {
+  long faults = 0;
+  for (uint64_t cap : {64ull, 256ull, 4096ull, 1ull << 20, 1ull << 28}) {
+    for (uint32_t level = 0; level <= kNoLevel; ++level) {
+      for (uint64_t room : {(uint64_t)0, (uint64_t)1, (uint64_t)2, (uint64_t)3, cap / 32, cap / 8, cap / 4 - 1, cap / 4, cap}) {
+        const uint32_t lim = secondary_limit((uint32_t)room, cap, level);
+        faults += lim > room || (room && !lim);
+        if (level == kNoLevel || !tight(room, cap)) faults += lim != room;
+        else if (room > 2) faults += lim == room;
+        const uint32_t stuck = next_level(level, 5, 0, room, cap, true), none = next_level(level, 0, 5, room, cap, true);
+        faults += stuck != (level + 4 < kNoLevel ? level + 4 : kNoLevel) || none < level;
+        for (bool little : {false, true}) faults += next_level(level, 5, 5, room, cap, little) > kNoLevel;
+      }
+    }
+    // full queues lower the level to the bottom
+    uint32_t level = kNoLevel;
+    for (int i = 0; i < 12; ++i) level = next_level(level, 1, 1, 0, cap, false);
+    faults += level != 0;
+  }
+  return faults;
+}
+
 }  // namespace
 
 int main() {
@@ -157,5 +182,7 @@ int main() {
   const long a = iterations<false>(false, &late), b = iterations<true>(false, &late);
   const long x = iterations<false>(true, &unused), y = iterations<true>(true, &unused);
   std::printf("%ld blocks started after a close; faults %ld, %ld; with one record %ld, %ld\n", late, a, b, x, y);
-  return a == 0 && b == 0 && late > 1000 && x > 0 && y > 0 ? 0 : 1;
+  const long l = limits();
+  std::printf("limits of scarce room: %ld faults\n", l);
+  return a == 0 && b == 0 && l == 0 && late > 1000 && x > 0 && y > 0 ? 0 : 1;
 }
