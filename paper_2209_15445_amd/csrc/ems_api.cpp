@@ -737,7 +737,7 @@ ems_status rt_create(const ems_config* cfg, const ems_geometry* geo, void* d_ws,
   }
   if (!no_alloc) c->pin_chk = reinterpret_cast<unsigned long long*>(c->pin_ctl + 1);
   // device table layout: photon block [mat][3][nodes], then lepton block
-  // [mat][10][nodes], in the arithmetic type of the chosen form
+  // [mat][12][nodes], in the arithmetic type of the chosen form
   std::vector<char> packed, elem;
   std::vector<MatRT> rt = c->ts.rt;
   if (cfg->precision == EMS_MIXED) {

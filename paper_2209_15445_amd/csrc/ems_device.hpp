@@ -101,7 +101,7 @@ EMS_HD void view_at(char* b, uint64_t cap, Queue<double>& q) {
 }
 EMS_HD void view_at(char* b, uint64_t, Queue<float>& q) { q.rec = reinterpret_cast<TrackRec32*>(b); }
 
-// Loop control, written by the last block of each step launch.
+// Loop control, written by the block that closes an iteration.
 //
 // Each next-queue buffer of capacity cap has two regions: survivors and
 // carried tracks of that species fill it from the bottom (home region), new
@@ -145,12 +145,12 @@ struct Ctl {
   Extents ext[2];
   uint32_t blocks_done;   // completion ticket of the running launch
   uint32_t iteration;
-  uint32_t live;          // tracks in the current queues (after the swap)
+  uint32_t live;          // tracks in the next iteration's queues
   uint32_t error;         // kErr* bits
   uint32_t peak[3];
   unsigned long long steps[3], created[3], deferred, log_n;
   unsigned long long visits[3];  // track records loaded (one per visit)
-  unsigned long long made_by[2];  // secondary records written (photon, e-/e+ launches)
+  unsigned long long made_by[2];  // secondary records written (photons, e-/e+)
   unsigned long long exit_n;  // outgoing tracks recorded (may exceed the capacity)
   unsigned long long steps_s;  // e- steps taken by the short launches
   // tallies of the running iteration, folded into the totals above when it
@@ -210,7 +210,7 @@ struct KArgs {
   double* edep;        // [rows][n_slabs]
   LedgerDev* ledger;   // [rows]
   const void* tab_g;   // photon table block [mat][3][nodes] (double or float)
-  const void* tab_l;   // lepton table block [mat][10][nodes]
+  const void* tab_l;   // lepton table block [mat][12][nodes]
   const double* zplane;
   const uint32_t* slab_mat;
   const MatRT* mat;
@@ -246,7 +246,7 @@ struct KArgs {
   // a buffer of their own (two of cap_s records, current and next) and take
   // their first step in a launch of their own at the start of the next
   // iteration; a track whose first step selects an interaction goes to the
-  // spill buffer (cap_p records) for the e-/e+ launch of that iteration.
+  // spill buffer (cap_p records) for the e-/e+ of that iteration's visit launch.
   char* sbase;                // the two short buffers, then the spill buffer
   uint64_t cap_s, cap_p;
   double short_E;

@@ -167,12 +167,13 @@ __device__ inline void serve(Ctl* ctl, Ranges& rg, const Ask (&a)[N]) {
   }
 }
 
-// Per-iteration append plan of species q (the same in both launches of an
-// iteration, computed from the current queue sizes).  The chunk is the
+// Per-iteration append plan by species (every wave of an iteration's launches
+// computes the same, from the current queue sizes).  The chunk is the
 // largest power of two up to EMS_APPEND_CHUNK for which all waves together
 // leave unused at most a quarter of the current population and of the free
 // room (so small populations append exactly); the secondary limit leaves
-// room for every survivor plus the unused chunk ends of the home region.
+// room for every survivor plus the unused chunk ends of the home region, and
+// less than that where room is scarce (secondary_limit).
 // 128: 40 000 x 10 GeV, mixed form, 104.5 ms, 10^4 x 10 GeV 40.6 (64: 108.0 and
 // 40.65, 256: 104.5 and 40.9, 1024: 109.5 and 41.2).
 #ifndef EMS_APPEND_CHUNK
@@ -1120,15 +1121,15 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
 
 // Short electrons.  Most e- secondaries of a shower are slow (Compton and
 // photo-electrons, delta rays) and end in their first step, ranged out.
-// In the e-/e+ launch each of them costs a lane a record load, one step and
+// In the visit launch each of them costs a lane a record load, one step and
 // a commit in a wave whose other lanes follow long tracks; here a launch of
 // its own, at the start of the iteration, gives every lane one such track:
 // one step, its tallies, and the survivor (if any) appended to the next e-
 // queue as any e-/e+ survivor.  A track whose first step selects a discrete
-// interaction is handed unchanged to this iteration's e-/e+ launch (spill
+// interaction is handed unchanged to this iteration's visit launch (spill
 // buffer), which takes the same step again and samples the interaction
 // there: every step still draws from its own (id, step) stream, so results
-// and the iteration of every step are those of the e-/e+ launch.
+// and the iteration of every step are those of the visit launch.
 // (without optional parts the step and a prefetched record fit 3 resident
 // waves per SIMD in FP64, 5 in FP32; with them 3 and 4; in box geometries
 // 2 and 3)
@@ -1363,15 +1364,18 @@ __global__ void k_census(KArgs a) {
 
 #endif  // EMS_SLAB_F32_TU
 
-// Kernel variants: the optional parts each kernel is built with: none, in a
-// slab stack the field, the field and the records (the offload server),
-// scattering and fluctuations, compounds with or without a field, or all.  A context launches the smallest variant that covers its
-// configuration (KArgs::feat).  A part that is compiled in costs registers
-// and spills also where it is off: against the variant with all parts, 1500 x
-// 10 GeV with scattering and fluctuations 14.78 -> 13.44 ms, PbWO4 1501
-// mixed-species events in a field, mixed form 17.09 -> 16.64, 37 x 1 GeV 2.38
-// -> 2.28; against the field with the records 2500 mixed-species events 27.83
-// -> 26.42, 48 tracks 0.364 -> 0.343.  (Not with the short-electron routing: each would be built twice.)
+// Kernel variants.  A part that is compiled in costs registers and spills also
+// where it is off, so a context launches the smallest variant that covers its
+// configuration (KArgs::feat).  Both kinds of geometry: no parts, or all.  A
+// slab stack also: the field; the field and the records (the offload server);
+// scattering and fluctuations; the field and compounds.  Variants with the
+// short-electron routing exist for no parts, the field and the records, and
+// all (each would be built twice otherwise).
+// Against the variant with all parts: 1500 x 10 GeV with scattering and
+// fluctuations 14.78 -> 13.44 ms, PbWO4 1501 mixed-species events in a field,
+// mixed form 17.09 -> 16.64, 37 x 1 GeV 2.38 -> 2.28; the field alone against
+// the field with the records: 2500 mixed-species events 27.83 -> 26.42 ms, 48
+// tracks 0.364 -> 0.343.
 template <class R, int GEO>
 const void* visit_fn(uint32_t feat) {
   if (feat == 0) return reinterpret_cast<const void*>(&k_visit<R, GEO, 0>);
