@@ -13,10 +13,10 @@ enum : uint32_t { kPhotons = 1u, kLeptons = 2u };
 // Scarce room goes to the lower energies.  A queue that is filled with tracks
 // whose next steps all need a slot never moves again, so queues too small for
 // a shower have to be kept from filling with tracks that take long to end.
-// Once an iteration had to carry tracks (steps refused for want of room), the
-// secondaries of a track above an energy 2^(level - 10) MeV take no room in a
-// queue less than a quarter of which is free, and an iteration takes at most
-// half of such a queue's room.  The level follows the room: down an octave an
+// Once an iteration had to carry tracks (steps refused for want of room), and
+// while less than a quarter of some queue is free, tracks above an energy of
+// 2^(level - 10) MeV make no secondaries (they are carried), and an iteration
+// takes at most half of such a queue's room.  The level follows the room: down an octave an
 // iteration while less than an eighth of a queue is free (two below a
 // thirty-second), up one while little of what there was is taken, up two when
 // nothing had to be carried, and up four when nothing moved at all; the batch
@@ -26,16 +26,19 @@ enum : uint32_t { kPhotons = 1u, kLeptons = 2u };
 // Queues that hold the whole shower never come to this.
 // Times in queues of a fourth, an eighth and a sixteenth of the largest
 // population, with this rule and (in brackets) with photons waiting while less
-// than an eighth of the e- queue was free: 500 x 2 GeV FP64 10.7, 34.5, 82.6 ms
-// (10.0, no end, no end), mixed form 9.9, 24.8, 60.8 (9.8, 38.6, no end), in
-// the tower block FP64 20.3, 77.6, 232 (20.0, 49.0, no end); 2000 x 5 GeV FP64
-// 19.3, 32.1, 54.6 (19.2, 32.0, 116.5).
+// than an eighth of the e- queue was free: 500 x 2 GeV FP64 10.6, 33.9, 70.6 ms
+// (10.0, no end, no end), mixed form 9.9, 23.6, 51.5 (9.8, 38.6, no end), in
+// the tower block FP64 21.2, 70.8, 161 (20.0, 49.0, no end); 2000 x 5 GeV FP64
+// 19.3, 32.2, 62.6 (19.2, 32.0, 116.5).  (Limited only where a secondary goes to
+// a scarce queue: 82.6 and 232 ms in a sixteenth, and more registers.)
 constexpr uint32_t kNoLevel = 24;  // (16 GeV: no limit)
 EMS_HD bool tight(uint64_t room, uint64_t cap) { return room < cap / 4; }
 EMS_HD uint32_t secondary_limit(uint32_t room, uint64_t cap, uint32_t level) {
   return level < kNoLevel && tight(room, cap) && room > 2 ? room - room / 2 : room;
 }
-EMS_HD float energy_limit(uint32_t level) { return __builtin_ldexpf(1.0f, (int)level - 10); }
+EMS_HD float energy_limit(uint32_t level) {
+  return level < kNoLevel ? __builtin_ldexpf(1.0f, (int)level - 10) : __builtin_huge_valf();
+}
 // least: free slots of the fullest next queue; little: at most a quarter of
 // every tight queue's limit was taken
 EMS_HD uint32_t next_level(uint32_t level, uint64_t carried, uint64_t commits, uint64_t least, uint64_t cap,

@@ -555,6 +555,7 @@ struct Launch {
   uint32_t cur;
   Sizes z;
   Plan plan;
+  float limit;  // MeV: tracks above it make no secondaries in this iteration
   uint32_t* cnt;  // block's tallies (LDS)
 };
 
@@ -717,14 +718,7 @@ __device__ __forceinline__ void visit_loop(Ctl* ctl, const Staged<R>& st, const 
         // its secondaries fit), then survivors or carried tracks
         // e- secondaries below short_E go to the next short buffer
         const bool made = done && o.nsec > 0;
-        bool hold = false;
-        if (ln.z.level < kNoLevel) {  // scarce room
-          const auto into = [&](int q) { return o.sec[0].sp == q || (o.nsec > 1 && o.sec[1].sp == q); };
-          const bool a_tight = tight(plan.lim[kSecA] + (kShort && kSecA == kElectron ? plan.lim_s : 0u), a.cap);
-          const bool b_tight = tight(plan.lim[kSecB] + (kShort && kSecB == kElectron ? plan.lim_s : 0u), a.cap);
-          hold = made && ((a_tight && into(kSecA)) || (b_tight && into(kSecB))) &&
-                 (float)e0 + (sp == 2 ? (float)(2.0 * kMe) : 0.0f) > energy_limit(ln.z.level);
-        }
+        const bool hold = made && (float)e0 + (sp == 2 ? (float)(2.0 * kMe) : 0.0f) > ln.limit;  // scarce room
         const bool s0 = shorts && made && !hold && o.sec[0].sp == kElectron && o.sec[0].E < a.short_E;
         const bool s1 = shorts && made && !hold && o.nsec > 1 && o.sec[1].sp == kElectron && o.sec[1].E < a.short_E;
         const bool in0 = made && !hold && !s0, in1 = made && !hold && o.nsec > 1 && !s1;  // to the queues
@@ -1060,6 +1054,10 @@ __global__ __launch_bounds__(kBlock, (visit_waves<R, GEO, F>())) void k_visit(KA
   ln.z = sizes_of<kShort>(ctl, ln.cur, a.cap_p);
   // secondary slots per species that leave room for all survivors
   ln.plan = append_plan<kShort>(a, ln.z.n0, ln.z.n1, ln.z.n2, ln.z.ns, ln.z.level);
+  bool any_tight = false;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) any_tight |= tight(ln.plan.lim[q] + (kShort && q == 1 ? ln.plan.lim_s : 0u), a.cap);
+  ln.limit = any_tight ? energy_limit(ln.z.level) : __builtin_huge_valf();
   const bool stop = ctl->ext[ln.cur].stop != 0;
   const uint32_t ng = which & kPhotons && !stop ? ln.z.n0 : 0u;
   const uint32_t nl = which & kLeptons && !stop ? ln.z.n1 + ln.z.n2 + ln.z.np : 0u;

@@ -167,6 +167,7 @@ long limits() {
         for (bool little : {false, true}) faults += next_level(level, 5, 5, room, cap, little) > kNoLevel;
       }
     }
+    faults += energy_limit(kNoLevel) < 1e30f || energy_limit(10) != 1.0f;
     // full queues lower the level to the bottom
     uint32_t level = kNoLevel;
     for (int i = 0; i < 12; ++i) level = next_level(level, 1, 1, 0, cap, false);
